@@ -1,7 +1,7 @@
 // Convolution, fully connected, loss and Adam kernels of the pose-proposal
 // network (BF16 operands on the matrix cores, FP32 accumulation).
 //
-// Every convolution pass is an implicit GEMM on one tile engine: a 256-thread
+// Every pass here is an implicit GEMM on one tile engine: a 256-thread
 // block computes a 64 x 64 tile of C = A B, staging 64 x KB slices of A and B
 // through LDS as bfloat16 and issuing gfx950's v_mfma_f32_16x16x32_bf16 (each
 // wavefront owns a 32 x 32 quarter: 2 x 2 MFMA tiles, 32 k per instruction;
@@ -11,9 +11,9 @@
 // straight from the NHWC activations, so no im2col buffer exists:
 //   forward          C[pixel_out][cout] = X_col[pixel_out][(tap,ci)] W[(tap,ci)][cout]
 //   backward (data)  C[pixel_in][ci]    = G_col[pixel_in][(tap,co)]  W[(tap,ci)][co]^T
-//   backward (wgt)   C[(tap,ci)|1][co]  = X_col^T[(tap,ci)|1][pixel] G[pixel][co]   (split over pixels)
 // with G = dL/dy masked by y > 0 (ReLU), taps (ky, kx) of a 3x3 window, the
-// width circular and the height zero-padded.
+// width circular and the height zero-padded.  The weight gradient contracts
+// over pixels and has kernels of its own (ups_cnn_wgrad.hip).
 #include <cstdint>
 
 #include "ups_cnn.hpp"
@@ -21,19 +21,8 @@
 namespace ups {
 
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-// round to nearest even
-__device__ __forceinline__ uint16_t f2bf(float f) {
-    uint32_t u = __float_as_uint(f);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
-__device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
 constexpr int kBM = 64, kBN = 64;
-constexpr int kSplitAlign = 16;                              // weight-gradient pixel chunks: multiples of this
 
 // One 64 x 64 tile: A rows m0.., B columns n0.., K range [k_begin, k_end).
 // LA::load(row, k, out[4]) / LB::load(col, k, out[4]) return bf16 values of
@@ -236,11 +225,6 @@ __global__ __launch_bounds__(256) void k_conv_fwd(ConvShape c, const uint16_t *_
 
 // ------------------------------------------------------ backward (data)
 
-// g = dy masked by y > 0, rounded to bf16
-__device__ __forceinline__ uint16_t grad_bf(const float *dy, const uint16_t *y, size_t idx) {
-    return (y[idx] != 0 && !(y[idx] & 0x8000)) ? f2bf(dy[idx]) : (uint16_t)0;
-}
-
 // A row = input pixel (b, iy, ix), column k = tap * cout + co: the output
 // gradient at the output pixel whose tap (ky, kx) reads (iy, ix), if any.
 struct LoadGradCol {
@@ -302,100 +286,6 @@ __global__ __launch_bounds__(256) void k_conv_bwd_data(ConvShape c, const uint16
               blockIdx.y * kBN, M, N, 0, K);
 }
 
-// ---------------------------------------------------- backward (weights)
-
-// A row r = (tap, ci) for r < 9 cin, the bias row (all ones) for r = 9 cin;
-// column k = output pixel.
-struct LoadIm2colT {
-    ConvShape c;
-    const uint16_t *x;
-    __device__ __forceinline__ void load(int r, int k, int k_end, uint16_t *o) const {
-        const int K9 = 9 * c.cin;
-        o[0] = o[1] = o[2] = o[3] = 0;
-        if (r > K9 || k >= k_end) return;
-        if (r == K9) {
-#pragma unroll
-            for (int e = 0; e < 4; e++) o[e] = (k + e < k_end) ? (uint16_t)0x3F80 : (uint16_t)0;  // 1.0
-            return;
-        }
-        const int tap = r / c.cin, ci = r - tap * c.cin;
-        const int ky = tap / 3, kx = tap - 3 * ky;
-        // the first pixel's (b, oy, ox) by division, the next three by stepping
-        int b = k / (c.ho * c.wo), q = k - b * c.ho * c.wo, oy = q / c.wo, ox = q - oy * c.wo;
-#pragma unroll
-        for (int e = 0; e < 4; e++) {
-            if (k + e < k_end) {
-                const int iy = c.stride * oy + ky - 1;
-                if (iy >= 0 && iy < c.h) {
-                    int ix = c.stride * ox + kx - 1;
-                    ix = ix < 0 ? ix + c.w : (ix >= c.w ? ix - c.w : ix);
-                    o[e] = x[((size_t)(b * c.h + iy) * c.w + ix) * c.cin + ci];
-                }
-            }
-            if (++ox == c.wo) {
-                ox = 0;
-                if (++oy == c.ho) {
-                    oy = 0;
-                    b++;
-                }
-            }
-        }
-    }
-};
-
-// B^T row n = co over k = output pixel: G[pixel][co].
-struct LoadGradT {
-    ConvShape c;
-    const float *dy;
-    const uint16_t *y;
-    __device__ __forceinline__ void load(int n, int k, int k_end, uint16_t *o) const {
-#pragma unroll
-        for (int e = 0; e < 4; e++)
-            o[e] = (n < c.cout && k + e < k_end) ? grad_bf(dy, y, (size_t)(k + e) * c.cout + n) : (uint16_t)0;
-    }
-};
-
-// blockIdx.z = split s over output pixels [s chunk, (s+1) chunk)
-__global__ __launch_bounds__(256) void k_conv_bwd_weight(ConvShape c, const uint16_t *__restrict__ x,
-                                                         const uint16_t *__restrict__ y, const float *__restrict__ dy,
-                                                         int chunk, float *__restrict__ part) {
-    const int M = 9 * c.cin + 1, N = c.cout, P = c.n * c.ho * c.wo;
-    const int kb = blockIdx.z * chunk, ke = min(P, kb + chunk);
-    mfma_tile(LoadIm2colT{c, x}, LoadGradT{c, dy, y}, StoreF32{part + (size_t)blockIdx.z * M * N, N},
-              blockIdx.x * kBM, blockIdx.y * kBN, M, N, kb, ke);
-}
-
-// dW[r][co] (r < 9 cin) and db[co] (the ones row): sum of the splits in order.
-__global__ __launch_bounds__(256) void k_conv_bwd_weight_reduce(int M, int N, int splits,
-                                                                const float *__restrict__ part, float *__restrict__ dw,
-                                                                float *__restrict__ db) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= M * N) return;
-    float s = 0.f;
-    for (int z = 0; z < splits; z++) s += part[(size_t)z * M * N + i];
-    const int r = i / N;
-    if (r < M - 1) dw[i] = s;
-    else db[i - r * N] = s;
-}
-
-// The same sums for few outputs and many splits (the first layers): one
-// wavefront per output, lane l adding splits l, l + 64, ... in order, then a
-// xor butterfly over the lanes (every lane ends with the same total).
-__global__ __launch_bounds__(256) void k_conv_bwd_weight_reduce_wave(int M, int N, int splits,
-                                                                     const float *__restrict__ part,
-                                                                     float *__restrict__ dw, float *__restrict__ db) {
-    const int i = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (i >= M * N) return;  // uniform per wavefront
-    float s = 0.f;
-    for (int z = lane; z < splits; z += 64) s += part[(size_t)z * M * N + i];
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) s += __shfl_xor(s, m, 64);
-    if (lane != 0) return;
-    const int r = i / N;
-    if (r < M - 1) dw[i] = s;
-    else db[i - r * N] = s;
-}
-
 // ------------------------------------------------------------ host side
 
 static int cdiv(int a, int b) { return (a + b - 1) / b; }
@@ -437,44 +327,6 @@ ups_status launch_conv_bwd_data(const ConvShape &c, const uint16_t *y, const flo
     const int M = c.n * c.h * c.w;
     if (M == 0) return UPS_OK;
     hipLaunchKernelGGL(k_conv_bwd_data, dim3(cdiv(M, kBM), cdiv(c.cin, kBN)), dim3(256), 0, s, c, y, dy, w_kn, dx);
-    UPS_CHECK_HIP(hipGetLastError());
-    return UPS_OK;
-}
-
-// Splits of the output pixels for the weight gradient: about 1024 blocks,
-// chunks a multiple of kSplitAlign and at least 64 pixels.
-static void wgt_split(const ConvShape &c, int &splits, int &chunk) {
-    const int M = 9 * c.cin + 1, P = c.n * c.ho * c.wo;
-    const int tiles = cdiv(M, kBM) * cdiv(c.cout, kBN);
-    splits = std::max(1, std::min(256, cdiv(1024, tiles)));
-    chunk = std::max(64, cdiv(cdiv(std::max(P, 1), splits), kSplitAlign) * kSplitAlign);
-    splits = cdiv(std::max(P, 1), chunk);
-}
-
-int64_t conv_wgt_work_floats(const ConvShape &c) {
-    int splits, chunk;
-    wgt_split(c, splits, chunk);
-    return (int64_t)splits * (9 * c.cin + 1) * c.cout;
-}
-
-ups_status launch_conv_bwd_weight(const ConvShape &c, const uint16_t *x, const uint16_t *y, const float *dy,
-                                  float *dw, float *db, float *work, int64_t work_floats, hipStream_t s) {
-    int splits, chunk;
-    wgt_split(c, splits, chunk);
-    const int M = 9 * c.cin + 1;
-    UPS_REQUIRE((int64_t)splits * M * c.cout <= work_floats, "weight-gradient workspace too small");
-    const int P = c.n * c.ho * c.wo;
-    if (P > 0) {
-        hipLaunchKernelGGL(k_conv_bwd_weight, dim3(cdiv(M, kBM), cdiv(c.cout, kBN), splits), dim3(256), 0, s, c, x, y,
-                           dy, chunk, work);
-        UPS_CHECK_HIP(hipGetLastError());
-    }
-    if (M * c.cout <= 32768 && splits >= 64)
-        hipLaunchKernelGGL(k_conv_bwd_weight_reduce_wave, dim3(cdiv(M * c.cout, 4)), dim3(256), 0, s, M, c.cout,
-                           P > 0 ? splits : 0, work, dw, db);
-    else
-        hipLaunchKernelGGL(k_conv_bwd_weight_reduce, dim3(cdiv(M * c.cout, 256)), dim3(256), 0, s, M, c.cout,
-                           P > 0 ? splits : 0, work, dw, db);
     UPS_CHECK_HIP(hipGetLastError());
     return UPS_OK;
 }

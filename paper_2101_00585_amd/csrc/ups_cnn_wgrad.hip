@@ -1,0 +1,426 @@
+// Weight and bias gradients of the 3x3 convolutions:
+//   dW[r][co] = sum over output pixels p of X_col[p][r] G[p][co],  r = (tap, ci),
+//   db[co]    = sum over p of G[p][co],
+// G = dL/dy masked by y > 0 (ReLU) and rounded to bfloat16.  The contraction
+// runs over pixels while both operands lie in memory with their channels
+// contiguous, so the blocks stage them as they lie ([pixel][row] and
+// [pixel][co] in LDS, 16-byte loads and stores) and the matrix-core fragments
+// come from gfx950's transposing LDS read (ds_read_b64_tr_b16): the lanes of a
+// 16-lane group supply the addresses of four pixels' 16-element rows and each
+// receives the four pixels of one row element.
+#include "ups_cnn.hpp"
+
+namespace ups {
+
+namespace {
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+
+struct WgradArgs {
+    ConvShape c;
+    const uint16_t *x, *y;
+    const float *dy;
+    float *part;  // [split][9 cin + 1][cout]
+    int chunk;    // output pixels of a split
+    // a step of `unit` output pixels in mixed radix (images, rows, columns)
+    // and what it adds to the centre offset; a wrap to the next row or image
+    int step_oy, step_ox;
+    uint32_t step_add, row_add, image_add;
+};
+
+// An output pixel (oy, ox) of some image and the offset in x of its window's
+// centre, moved along without divisions (which cost more than the rest of
+// the staging: the blocks are bound by its instructions, not by memory).
+struct PixelWalk {
+    int oy, ox;
+    uint32_t centre;
+    __device__ __forceinline__ void start(const ConvShape &c, int p) {
+        const int b = p / (c.ho * c.wo), q = p - b * c.ho * c.wo;
+        oy = q / c.wo, ox = q - oy * c.wo;
+        centre = (uint32_t)((b * c.h + c.stride * oy) * c.w + c.stride * ox) * (uint32_t)c.cin;
+    }
+    __device__ __forceinline__ void wrap(const WgradArgs &a) {
+        if (ox >= a.c.wo) ox -= a.c.wo, oy++, centre += a.row_add;
+        if (oy >= a.c.ho) oy -= a.c.ho, centre += a.image_add;
+    }
+    __device__ __forceinline__ void step(const WgradArgs &a) {
+        ox += a.step_ox, oy += a.step_oy, centre += a.step_add;
+        wrap(a);
+    }
+    __device__ __forceinline__ void next(const WgradArgs &a) {
+        ox++, centre += a.c.stride * a.c.cin;
+        wrap(a);
+    }
+};
+
+// Where tap (ky, kx) of a window lies: `off` from the centre, `wrap_add` more
+// on output column `wrap_ox` (the width is circular), nowhere on output row
+// `no_oy` (the height is zero-padded).
+struct Tap {
+    int off, wrap_add, wrap_ox, no_oy;
+    __device__ __forceinline__ Tap(const ConvShape &c, int ky, int kx) {
+        off = ((ky - 1) * c.w + kx - 1) * c.cin;
+        wrap_add = kx == 0 ? c.w * c.cin : -c.w * c.cin;
+        wrap_ox = kx == 0 ? 0 : (kx == 2 && c.stride * (c.wo - 1) + 1 == c.w) ? c.wo - 1 : -1;
+        no_oy = ky == 0 ? 0 : (ky == 2 && c.stride * (c.ho - 1) + 1 >= c.h) ? c.ho - 1 : -1;
+    }
+    __device__ __forceinline__ bool inside(const PixelWalk &w) const { return w.oy != no_oy; }
+    __device__ __forceinline__ uint32_t at(const PixelWalk &w) const {
+        return w.centre + off + (w.ox == wrap_ox ? wrap_add : 0);
+    }
+};
+
+// Four masked gradients in bfloat16: dy where y > 0.
+__device__ __forceinline__ uint2 masked_grad4(uint2 y, float4 g) {
+    const uint2 h = bf16x4_of(g);
+    auto keep = [](uint32_t y2, uint32_t h2) {  // y as a signed integer is positive where it is not a zero and has no sign
+        return ((int)(y2 << 16) > 0 ? h2 & 0xFFFFu : 0) | ((int)y2 > 0xFFFF ? h2 & 0xFFFF0000u : 0);
+    };
+    return make_uint2(keep(y.x, h.x), keep(y.y, h.y));
+}
+
+// Fragment of rows e0 .. e0+15 over the 32 pixels from p0 of an LDS image
+// [pixel][element] of `pitch` bytes.  Element order of the contraction: lane
+// group g holds pixels 4g .. 4g+3 and 16+4g .. 16+4g+3 (the same for both
+// operands), so the sixteen 32-byte rows of one read fall on different banks
+// when the pitch is an odd multiple of 32 bytes.
+__device__ __forceinline__ bf16x8 tr_fragment(const uint8_t *base, int pitch, int p0, int e0) {
+    const int l = threadIdx.x & 63, px = p0 + 4 * (l >> 4) + ((l & 15) >> 2);
+    const uint8_t *p = base + px * pitch + 2 * e0 + 8 * (l & 3);
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)p);
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 16 * pitch));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+constexpr int kRowTile = 288, kPix = 64, kWideThreads = 576;
+
+// Wide form: a block of nine wavefronts owns kRowTile rows r and NF * 16
+// output channels (each wavefront 32 rows) over one split of the pixels, 64
+// pixels a step; 288 rows are all nine taps of 32 channels, so few blocks
+// read a gradient.  Bound by a step's round trips (window loads, LDS, barrier)
+// with about one block a CU, which the workspace of the splits' sums sets; so
+// two steps' loads are in flight and two LDS buffers leave one barrier a step.
+// Layers of 32 -> 64, 64 -> 96, 96 -> 128 and 128 -> 128 channels at batch
+// 256: 25.7, 26.6, 16.7 and 18.7 us with the reduction, against 177.5, 165.6,
+// 68.6 and 78 on 64 x 64 tiles gathered along pixels by 2-byte loads.  UNIT:
+// elements per load of x (8 where cin is a multiple of 8, 2 where it is even,
+// else 1).
+template <int NF, int UNIT>
+__global__ __launch_bounds__(kWideThreads) void k_conv_wgrad(WgradArgs a) {
+    constexpr int kXP = kRowTile * 2 + 32;                      // 19 x 32 bytes
+    constexpr int kGP = (NF % 2) ? NF * 32 + 64 : NF * 32 + 32;  // an odd multiple of 32 bytes
+    __shared__ __align__(16) uint8_t xs[2][kPix * kXP];
+    __shared__ __align__(16) uint8_t gs[2][kPix * kGP];
+    const ConvShape &c = a.c;
+    // the wavefront's number as a scalar: MFMA ignores the execution mask, so what it guards has to be a scalar branch
+    const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+    const int rows = 9 * c.cin, row0 = blockIdx.x * kRowTile, co0 = blockIdx.y * NF * 16;
+    const int p_begin = blockIdx.z * a.chunk, p_end = min(c.n * c.ho * c.wo, p_begin + a.chunk);
+    // staging: 8 rows of four consecutive pixels of each step, and 8 channels of one pixel
+    const int r8 = t % 36, pr = 4 * (t / 36), r = row0 + 8 * r8;
+    const int tap = r / c.cin, ci = r - tap * c.cin;
+    const Tap at(c, tap / 3, tap % 3);
+    PixelWalk px;
+    px.start(c, p_begin + pr);
+    const int gp = t / (2 * NF), gc = co0 + 8 * (t % (2 * NF));
+    struct Staged {
+        uint4 x[4];
+        float4 dy[2];
+        uint2 y[2];
+    } st[2];
+    auto fetch = [&](Staged &f, int p0) {
+        PixelWalk w = px;
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const int p = p0 + pr + i;
+            f.x[i] = make_uint4(0, 0, 0, 0);
+            if constexpr (UNIT == 8) {
+                if (p < p_end && r < rows && at.inside(w)) f.x[i] = load_u4(a.x + at.at(w) + ci);
+            } else {
+                uint32_t v[4] = {0, 0, 0, 0};
+                if (p < p_end)
+#pragma unroll
+                    for (int e = 0; e < 8; e += UNIT) {
+                        const int re = r + e, te = re / c.cin, ce = re - te * c.cin;
+                        const Tap ate(c, te / 3, te % 3);
+                        if (re < rows && ate.inside(w)) {
+                            if constexpr (UNIT == 2) v[e >> 1] = *(const uint32_t *)(a.x + ate.at(w) + ce);
+                            else v[e >> 1] |= (uint32_t)a.x[ate.at(w) + ce] << (16 * (e & 1));
+                        }
+                    }
+                f.x[i] = make_uint4(v[0], v[1], v[2], v[3]);
+            }
+            if (i < 3) w.next(a);
+        }
+        px.step(a);
+        if (gp < kPix)
+#pragma unroll
+            for (int hh = 0; hh < 2; hh++) {
+                const int p = p0 + gp, co = gc + 4 * hh;
+                f.dy[hh] = make_float4(0.f, 0.f, 0.f, 0.f);
+                f.y[hh] = make_uint2(0, 0);
+                if (p < p_end && co < c.cout) {
+                    const size_t o = (size_t)p * c.cout + co;
+                    f.dy[hh] = load_f4(a.dy + o);
+                    f.y[hh] = load_u2(a.y + o);
+                }
+            }
+    };
+    f32x4 acc[2][NF], accb = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int m = 0; m < 2; m++)
+#pragma unroll
+        for (int f = 0; f < NF; f++) acc[m][f] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const bool bias = blockIdx.x == 0 && wave < NF;  // this wavefront also sums channels 16 wave ..
+    constexpr uint16_t one = 0x3F80;
+    const bf16x8 ones = __builtin_bit_cast(bf16x8, s16x8{one, one, one, one, one, one, one, one});
+    auto step = [&](Staged &f, int buf, int p0) {
+        uint8_t *x = xs[buf], *g = gs[buf];
+#pragma unroll
+        for (int i = 0; i < 4; i++) *(uint4 *)(x + (pr + i) * kXP + 16 * r8) = f.x[i];
+        if (gp < kPix) {
+            const uint2 lo = masked_grad4(f.y[0], f.dy[0]), hi = masked_grad4(f.y[1], f.dy[1]);
+            *(uint4 *)(g + gp * kGP + 16 * (t % (2 * NF))) = make_uint4(lo.x, lo.y, hi.x, hi.y);
+        }
+        // the buffer's readers of two steps ago passed the last step's barrier
+        __syncthreads();
+        if (p0 + 2 * kPix < p_end) fetch(f, p0 + 2 * kPix);
+#pragma unroll
+        for (int kc = 0; kc < kPix; kc += 32) {
+            bf16x8 fx[2], fg[NF];
+#pragma unroll
+            for (int m = 0; m < 2; m++) fx[m] = tr_fragment(x, kXP, kc, 32 * wave + 16 * m);
+#pragma unroll
+            for (int k = 0; k < NF; k++) fg[k] = tr_fragment(g, kGP, kc, 16 * k);
+            // channels as the result's rows: a lane ends with four consecutive channels of one r
+#pragma unroll
+            for (int k = 0; k < NF; k++) {
+#pragma unroll
+                for (int m = 0; m < 2; m++)
+                    acc[m][k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fg[k], fx[m], acc[m][k], 0, 0, 0);
+                if (bias && k == wave) accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fg[k], ones, accb, 0, 0, 0);
+            }
+        }
+    };
+    if (p_begin < p_end) fetch(st[0], p_begin);
+    if (p_begin + kPix < p_end) fetch(st[1], p_begin + kPix);
+    for (int p0 = p_begin; p0 < p_end; p0 += 2 * kPix) {
+        step(st[0], 0, p0);
+        if (p0 + kPix < p_end) step(st[1], 1, p0 + kPix);
+    }
+    float *part = a.part + (size_t)blockIdx.z * (rows + 1) * c.cout;
+#pragma unroll
+    for (int m = 0; m < 2; m++) {
+        const int row = row0 + 32 * wave + 16 * m + (lane & 15);
+        if (row < rows)
+#pragma unroll
+            for (int f = 0; f < NF; f++) {
+                const int co = co0 + 16 * f + 4 * (lane >> 4);
+                if (co < c.cout) store_f4(part + (size_t)row * c.cout + co, acc[m][f]);
+            }
+    }
+    if (bias && (lane & 15) == 0) {
+        const int co = co0 + 16 * wave + 4 * (lane >> 4);
+        if (co < c.cout) store_f4(part + (size_t)rows * c.cout + co, accb);
+    }
+}
+
+// Narrow form, for cin <= 3 (at most 27 rows, and the bias as one more row of
+// ones, so that the 288-row tile would be nine tenths empty): bound by reading
+// the gradients, so every wavefront streams its own pixels, 32 a step through
+// its own 6 KB of LDS without block barriers (the next step's loads in
+// flight), and the block's sixteen sums are added in wavefront order at the
+// end.  2 -> 32 channels, 524288 pixels: 25 us (109 MB at 5.3 TB/s without
+// the reduction's 5 us) against 335 on 64 x 64 tiles.
+constexpr int kNarrowWaves = 16;
+
+template <int CIN>
+__global__ __launch_bounds__(64 * kNarrowWaves) void k_conv_wgrad_narrow(WgradArgs a) {
+    constexpr int kP = 96;                // bytes per pixel: 32 elements, an odd multiple of 32
+    constexpr int kWaveBytes = 64 * kP;   // 32 pixels of x, 32 of the gradient
+    __shared__ __align__(16) uint8_t lds[kNarrowWaves * kWaveBytes];
+    const ConvShape &c = a.c;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    uint8_t *xs = lds + wave * kWaveBytes, *gs = xs + 32 * kP;
+    constexpr int rows = 9 * CIN;
+    const int co0 = blockIdx.y * 32;
+    const int p_begin = blockIdx.z * a.chunk, p_end = min(c.n * c.ho * c.wo, p_begin + a.chunk);
+    // staging: lane's pixel lane % 32, taps 0-4 (lower half) or 5-8 and the row of ones; gradients 4 channels at a time
+    const int px = lane & 31, half = lane >> 5;
+    for (int i = lane; i < kWaveBytes / 16; i += 64) *(uint4 *)(xs + 16 * i) = make_uint4(0, 0, 0, 0);
+    uint16_t xv[5][CIN];
+    float4 gd[4];
+    uint2 gy[4];
+    PixelWalk w;
+    w.start(c, p_begin + 32 * wave + px);
+    auto fetch = [&](int p0) {
+        const int p = p0 + px;
+#pragma unroll
+        for (int k = 0; k < 5; k++) {
+            const int tap = 5 * half + k;
+            const Tap at(c, tap / 3, tap % 3);
+            const bool on = p < p_end && tap < 9 && at.inside(w);
+            if constexpr (CIN == 2) {
+                const uint32_t v = on ? *(const uint32_t *)(a.x + at.at(w)) : 0;
+                xv[k][0] = v & 0xFFFF, xv[k][1] = v >> 16;
+            } else {
+#pragma unroll
+                for (int e = 0; e < CIN; e++) xv[k][e] = on ? a.x[at.at(w) + e] : 0;
+            }
+        }
+        w.step(a);
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const int pg = p0 + (lane >> 3) + 8 * k, co = co0 + 4 * (lane & 7);
+            gd[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+            gy[k] = make_uint2(0, 0);
+            if (pg < p_end && co < c.cout) {
+                const size_t o = (size_t)pg * c.cout + co;
+                gd[k] = load_f4(a.dy + o);
+                gy[k] = load_u2(a.y + o);
+            }
+        }
+    };
+    f32x4 acc[2][2];
+#pragma unroll
+    for (int m = 0; m < 2; m++)
+#pragma unroll
+        for (int f = 0; f < 2; f++) acc[m][f] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int step = 32 * kNarrowWaves;
+    int p0 = p_begin + 32 * wave;
+    if (p0 < p_end) fetch(p0);
+    for (; p0 < p_end; p0 += step) {
+#pragma unroll
+        for (int k = 0; k < 5; k++) {
+            const int tap = 5 * half + k;
+            if (tap < 9) {
+                uint16_t *d = (uint16_t *)(xs + px * kP) + tap * CIN;
+                if constexpr (CIN == 2) *(uint32_t *)d = xv[k][0] | ((uint32_t)xv[k][1] << 16);
+                else
+#pragma unroll
+                    for (int e = 0; e < CIN; e++) d[e] = xv[k][e];
+            } else {
+                ((uint16_t *)(xs + px * kP))[rows] = 0x3F80;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; k++)
+            *(uint2 *)(gs + ((lane >> 3) + 8 * k) * kP + 8 * (lane & 7)) = masked_grad4(gy[k], gd[k]);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        if (p0 + step < p_end) fetch(p0 + step);
+        bf16x8 fx[2], fg[2];
+#pragma unroll
+        for (int m = 0; m < 2; m++) fx[m] = tr_fragment(xs, kP, 0, 16 * m), fg[m] = tr_fragment(gs, kP, 0, 16 * m);
+#pragma unroll
+        for (int f = 0; f < 2; f++)
+#pragma unroll
+            for (int m = 0; m < 2; m++)
+                acc[m][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fg[f], fx[m], acc[m][f], 0, 0, 0);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+    __syncthreads();
+    // this wavefront's 32 x 32 sums, [r][co]
+    float *sums = (float *)(lds + wave * kWaveBytes);
+#pragma unroll
+    for (int m = 0; m < 2; m++)
+#pragma unroll
+        for (int f = 0; f < 2; f++)
+            *(f32x4 *)(sums + (16 * m + (lane & 15)) * 32 + 16 * f + 4 * (lane >> 4)) = acc[m][f];
+    __syncthreads();
+    const int r = threadIdx.x >> 5, co = co0 + (threadIdx.x & 31);
+    if (r <= rows && co < c.cout) {
+        float s = 0.f;
+#pragma unroll
+        for (int w = 0; w < kNarrowWaves; w++) s += ((const float *)(lds + w * kWaveBytes))[threadIdx.x];
+        a.part[((size_t)blockIdx.z * (rows + 1) + r) * c.cout + co] = s;
+    }
+}
+
+// dW and db: the splits' sums added in a fixed order.  A block owns 64 groups
+// of four outputs; its sixteen wavefronts each add every sixteenth split, so
+// that many loads of the latency-bound column are in flight, then the
+// sixteen sums are added in order.
+constexpr int kReduceThreads = 1024;
+
+__global__ __launch_bounds__(kReduceThreads) void k_conv_wgrad_reduce(int M, int N, int splits,
+                                                                      const float *__restrict__ part,
+                                                                      float *__restrict__ dw, float *__restrict__ db) {
+    __shared__ float4 red[16][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t q = (int64_t)blockIdx.x * 64 + lane, count = (int64_t)M * N, total = count / 4;  // N is a multiple of 4
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (q < total)
+#pragma unroll 4
+        for (int z = wave; z < splits; z += 16) {
+            const float4 v = load_f4(part + z * count + 4 * q);
+            s.x += v.x, s.y += v.y, s.z += v.z, s.w += v.w;
+        }
+    red[wave][lane] = s;
+    __syncthreads();
+    if (wave != 0 || q >= total) return;
+#pragma unroll
+    for (int w = 1; w < 16; w++) {
+        const float4 v = red[w][lane];
+        s.x += v.x, s.y += v.y, s.z += v.z, s.w += v.w;
+    }
+    const int64_t i = 4 * q, last = (int64_t)(M - 1) * N;
+    float *o = i < last ? dw + i : db + (i - last);
+    o[0] = s.x, o[1] = s.y, o[2] = s.z, o[3] = s.w;
+}
+
+int cdiv(int a, int b) { return (a + b - 1) / b; }
+
+// The most splits of the pixels whose partial sums the workspace holds.
+int max_splits(const ConvShape &c) {
+    const int tiles = cdiv(9 * c.cin + 1, 64) * cdiv(c.cout, 64), P = std::max(c.n * c.ho * c.wo, 1);
+    const int splits = std::max(1, std::min(256, cdiv(1024, tiles)));
+    return cdiv(P, std::max(64, cdiv(cdiv(P, splits), 16) * 16));
+}
+
+template <int NF>
+void launch_wide(const WgradArgs &a, dim3 grid, hipStream_t s) {
+    if (a.c.cin % 8 == 0) hipLaunchKernelGGL((k_conv_wgrad<NF, 8>), grid, dim3(kWideThreads), 0, s, a);
+    else if (a.c.cin % 2 == 0) hipLaunchKernelGGL((k_conv_wgrad<NF, 2>), grid, dim3(kWideThreads), 0, s, a);
+    else hipLaunchKernelGGL((k_conv_wgrad<NF, 1>), grid, dim3(kWideThreads), 0, s, a);
+}
+
+}  // namespace
+
+int64_t conv_wgt_work_floats(const ConvShape &c) { return (int64_t)max_splits(c) * (9 * c.cin + 1) * c.cout; }
+
+ups_status launch_conv_bwd_weight(const ConvShape &c, const uint16_t *x, const uint16_t *y, const float *dy,
+                                  float *dw, float *db, float *work, int64_t work_floats, hipStream_t s) {
+    const int M = 9 * c.cin + 1, P = c.n * c.ho * c.wo;
+    UPS_REQUIRE(conv_wgt_work_floats(c) <= work_floats, "weight-gradient workspace too small");
+    int splits = 0;
+    if (P > 0) {
+        WgradArgs a{c, x, y, dy, work, 0, 0, 0, 0, 0, 0};
+        const bool narrow = c.cin <= 3;
+        const int unit = narrow ? 32 * kNarrowWaves : kPix, row_tiles = narrow ? 1 : cdiv(9 * c.cin, kRowTile);
+        // 64 channels a block: half the staged windows of 32 for the same products (batch 256, 32 -> 64 and 64 -> 96
+        // channels: 25.7 and 26.6 us against 36.0 and 36.9); 32 where there are no more
+        const int nf = narrow || c.cout <= 32 ? 2 : 4;
+        a.chunk = cdiv(cdiv(P, max_splits(c)), unit) * unit;
+        splits = cdiv(P, a.chunk);
+        const int s_oy = unit / c.wo % c.ho, s_b = unit / (c.ho * c.wo);
+        a.step_oy = s_oy, a.step_ox = unit % c.wo;
+        a.step_add = ((uint32_t)(s_b * c.h + c.stride * s_oy) * c.w + c.stride * a.step_ox) * (uint32_t)c.cin;
+        a.row_add = (uint32_t)(c.stride * (c.w - c.wo)) * (uint32_t)c.cin;
+        a.image_add = (uint32_t)((c.h - c.stride * c.ho) * c.w) * (uint32_t)c.cin;
+        const dim3 grid(row_tiles, cdiv(c.cout, 16 * nf), splits);
+        if (c.cin == 1) hipLaunchKernelGGL(k_conv_wgrad_narrow<1>, grid, dim3(64 * kNarrowWaves), 0, s, a);
+        else if (c.cin == 2) hipLaunchKernelGGL(k_conv_wgrad_narrow<2>, grid, dim3(64 * kNarrowWaves), 0, s, a);
+        else if (c.cin == 3) hipLaunchKernelGGL(k_conv_wgrad_narrow<3>, grid, dim3(64 * kNarrowWaves), 0, s, a);
+        else if (nf == 2) launch_wide<2>(a, grid, s);
+        else launch_wide<4>(a, grid, s);
+        UPS_CHECK_HIP(hipGetLastError());
+    }
+    hipLaunchKernelGGL(k_conv_wgrad_reduce, dim3((unsigned)(((int64_t)M * c.cout / 4 + 63) / 64)), dim3(kReduceThreads), 0, s, M, c.cout,
+                       splits, work, dw, db);
+    UPS_CHECK_HIP(hipGetLastError());
+    return UPS_OK;
+}
+
+}  // namespace ups

@@ -83,6 +83,29 @@ def test_conv_backward(gpu_lib, shape):
         assert err < 2e-5, (what, err)
 
 
+# the weight gradient's tiles: 288 rows (9 cin), 32 or 64 channels, steps of 64 pixels (wide form) or 512 (cin <= 3),
+# loads of 8, 2 and 1 elements, split and single-split pixel ranges, windows that wrap onto themselves
+WGRAD_SHAPES = [(1, 1, 2, 32, 4, 2), (1, 3, 6, 8, 36, 1), (2, 5, 13, 33, 64, 1), (3, 4, 22, 34, 68, 2),
+                (1, 9, 64, 40, 32, 1), (9, 7, 18, 64, 96, 2), (2, 16, 17, 65, 12, 1), (1, 2, 2, 1, 4, 1),
+                (3, 11, 34, 3, 40, 1), (4, 16, 66, 2, 32, 1), (7, 16, 32, 1, 8, 2)]
+
+
+@pytest.mark.parametrize("shape", WGRAD_SHAPES, ids=[f"n{s[0]}_{s[1]}x{s[2]}_{s[3]}to{s[4]}_s{s[5]}" for s in WGRAD_SHAPES])
+def test_conv_weight_gradient_tile_edges(gpu_lib, shape):
+    """Each element within the FP32 accumulation bound P 2^-24 sum |x g| of its P terms."""
+    n, h, w, cin, cout, s = shape
+    x, W, b = _layer_case(shape, 400 + h + cin)
+    r = _rng(500 + cout)
+    y = C.bf16_round(C.relu(C.conv_forward(x, W, b, s)))
+    dy = C.bf16_round(r.normal(size=y.shape))
+    _, dW_ref, db_ref = C.conv_backward(x, y, dy, W, s)
+    _, dW_abs, db_abs = C.conv_backward(np.abs(x), y, np.abs(dy), W, s)
+    dW, db = gpu_lib.conv3x3_backward_weight(_bf(x), _bf(y), _f32(dy), s)
+    bound = y[..., 0].size * EPS32
+    assert (np.abs(_np(dW) - dW_ref) <= bound * dW_abs).all(), np.abs(_np(dW) - dW_ref).max()
+    assert (np.abs(_np(db) - db_ref) <= bound * db_abs).all(), np.abs(_np(db) - db_ref).max()
+
+
 def test_conv_empty_batch(gpu_lib):
     import torch
     x = torch.zeros((0, 8, 16, 4), dtype=torch.bfloat16, device="cuda")
