@@ -1,11 +1,13 @@
 // Convolution, fully connected, loss and Adam kernels of the pose-proposal
 // network (BF16 operands on the matrix cores, FP32 accumulation).
 //
-// Every pass here is an implicit GEMM on one tile engine: a 256-thread
-// block computes a 64 x 64 tile of C = A B, staging 64 x KB slices of A and B
-// through LDS as bfloat16 and issuing gfx950's v_mfma_f32_16x16x32_bf16 (each
-// wavefront owns a 32 x 32 quarter: 2 x 2 MFMA tiles, 32 k per instruction;
-// v_mfma_f32_16x16x16_bf16 when K is at most 32 and the slice is 16 wide).
+// The convolution passes here take the shapes that the streaming kernels of
+// ups_cnn_conv.hip do not (contracted channels that are no multiple of 8,
+// tensors past 2 GiB, a data gradient of stride 2 over more than 128 channels):
+// implicit GEMMs on one tile engine, where a 256-thread block computes a 64 x
+// 64 tile of C = A B, staging 64 x 32 slices of A and B through LDS as
+// bfloat16 and issuing gfx950's v_mfma_f32_16x16x32_bf16 (each wavefront owns
+// a 32 x 32 quarter: 2 x 2 MFMA tiles, 32 k per instruction).
 // The K loop loads the next slice into registers while the matrix cores work
 // on the current one.  Operand loaders gather A and B
 // straight from the NHWC activations, so no im2col buffer exists:
@@ -20,22 +22,19 @@
 
 namespace ups {
 
-typedef short bf16x4 __attribute__((ext_vector_type(4)));
-
 constexpr int kBM = 64, kBN = 64;
 
 // One 64 x 64 tile: A rows m0.., B columns n0.., K range [k_begin, k_end).
 // LA::load(row, k, out[4]) / LB::load(col, k, out[4]) return bf16 values of
 // A(row, k..k+3) / B(k..k+3, col), zero outside the operand; ST::store(row,
 // col, v) writes one result.
-template <int KB = 32, class LA, class LB, class ST>
+template <class LA, class LB, class ST>
 __device__ __forceinline__ void mfma_tile(const LA &la, const LB &lb, const ST &st, int m0, int n0, int M, int N,
                                           int k_begin, int k_end) {
-    // 32-wide k chunks on the 16x16x32 instruction when the slice holds them
-    constexpr bool kX32 = KB % 32 == 0;
+    constexpr int KB = 32;
     // LDS row pitch (elements), padded to spread the rows over the banks and
     // keeping each row 16-byte aligned for the 8-element fragment loads
-    constexpr int kLP = kX32 ? KB + 8 : KB + 4;
+    constexpr int kLP = KB + 8;
     constexpr int kQ = KB / 16;  // k quads per thread and operand in one slice
     __shared__ __align__(16) uint16_t As[kBM * kLP];
     __shared__ __align__(16) uint16_t Bs[kBN * kLP];
@@ -67,42 +66,20 @@ __device__ __forceinline__ void mfma_tile(const LA &la, const LB &lb, const ST &
         __syncthreads();
         // the next slice's loads are in flight while this slice is multiplied
         if (k0 + KB < k_end) fetch(k0 + KB);
-        // chunks of the slice in ascending k.  Lane l carries row (A) or
-        // column (B) l % 16 and the chunk's k = w (l / 16) .. w (l / 16) + w-1
-        // (w = 8 or 4 elements): the same k in the same slot of both operands
-        if constexpr (kX32) {
+        // lane l carries row (A) or column (B) l % 16 and the slice's k =
+        // 8 (l / 16) .. + 7: the same k in the same slot of both operands
+        bf16x8 fa[2], fb[2];
 #pragma unroll
-            for (int kc = 0; kc < KB / 32; kc++) {
-                bf16x8 fa[2], fb[2];
+        for (int i = 0; i < 2; i++)
+            fa[i] = *(const bf16x8 *)&As[(32 * wm + 16 * i + (lane & 15)) * kLP + 8 * (lane >> 4)];
 #pragma unroll
-                for (int i = 0; i < 2; i++)
-                    fa[i] = *(const bf16x8 *)&As[(32 * wm + 16 * i + (lane & 15)) * kLP + 32 * kc + 8 * (lane >> 4)];
+        for (int j = 0; j < 2; j++)
+            fb[j] = *(const bf16x8 *)&Bs[(32 * wn + 16 * j + (lane & 15)) * kLP + 8 * (lane >> 4)];
 #pragma unroll
-                for (int j = 0; j < 2; j++)
-                    fb[j] = *(const bf16x8 *)&Bs[(32 * wn + 16 * j + (lane & 15)) * kLP + 32 * kc + 8 * (lane >> 4)];
+        for (int i = 0; i < 2; i++)
 #pragma unroll
-                for (int i = 0; i < 2; i++)
-#pragma unroll
-                    for (int j = 0; j < 2; j++)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
-            }
-        } else {
-#pragma unroll
-            for (int kc = 0; kc < kQ; kc++) {
-                bf16x4 fa[2], fb[2];
-#pragma unroll
-                for (int i = 0; i < 2; i++)
-                    fa[i] = *(const bf16x4 *)&As[(32 * wm + 16 * i + (lane & 15)) * kLP + 16 * kc + 4 * (lane >> 4)];
-#pragma unroll
-                for (int j = 0; j < 2; j++)
-                    fb[j] = *(const bf16x4 *)&Bs[(32 * wn + 16 * j + (lane & 15)) * kLP + 16 * kc + 4 * (lane >> 4)];
-#pragma unroll
-                for (int i = 0; i < 2; i++)
-#pragma unroll
-                    for (int j = 0; j < 2; j++)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(fa[i], fb[j], acc[i][j], 0, 0, 0);
-            }
-        }
+            for (int j = 0; j < 2; j++)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
         __syncthreads();
     }
     // D[4 (lane/16) + e][lane % 16] of each 16 x 16 tile
@@ -214,12 +191,11 @@ struct StoreReluBf16 {
     }
 };
 
-template <int KB>
 __global__ __launch_bounds__(256) void k_conv_fwd(ConvShape c, const uint16_t *__restrict__ x,
                                                   const uint16_t *__restrict__ w_nk, const float *__restrict__ bias,
                                                   uint16_t *__restrict__ y) {
     const int M = c.n * c.ho * c.wo, N = c.cout, K = 9 * c.cin;
-    mfma_tile<KB>(LoadIm2col{c, x, 1.f / (float)c.cin}, LoadRowsBf16{w_nk, N, K}, StoreReluBf16{bias, y, N}, blockIdx.x * kBM,
+    mfma_tile(LoadIm2col{c, x, 1.f / (float)c.cin}, LoadRowsBf16{w_nk, N, K}, StoreReluBf16{bias, y, N}, blockIdx.x * kBM,
               blockIdx.y * kBN, M, N, 0, K);
 }
 
@@ -298,6 +274,15 @@ ConvShape conv_shape(int n, int h, int w, int cin, int cout, int stride) {
     return c;
 }
 
+WalkArgs walk_args(const ConvShape &c, int unit) {
+    const int b = unit / (c.ho * c.wo), oy = unit / c.wo % c.ho, ox = unit % c.wo;
+    WalkArgs a{c, oy, ox, 0, 0, 0};
+    a.step_add = ((uint32_t)(b * c.h + c.stride * oy) * c.w + c.stride * ox) * (uint32_t)c.cin;
+    a.row_add = (uint32_t)(c.stride * (c.w - c.wo)) * (uint32_t)c.cin;
+    a.image_add = (uint32_t)((c.h - c.stride * c.ho) * c.w) * (uint32_t)c.cin;
+    return a;
+}
+
 ups_status conv_check(const ConvShape &c) {
     UPS_REQUIRE(c.n >= 0 && c.h >= 1 && c.w >= 2 && c.cin >= 1 && c.cin <= 65536 && c.cout >= 4 &&
                     c.cout <= 65536 && (c.cout & 3) == 0,
@@ -313,11 +298,9 @@ ups_status launch_conv_fwd(const ConvShape &c, const uint16_t *x, const uint16_t
                            hipStream_t s) {
     const int M = c.n * c.ho * c.wo;
     if (M == 0) return UPS_OK;
-    // a small K (the first layer's 9 x 2 = 18) wastes less in 16-wide slices
-    if (9 * c.cin <= 32)
-        hipLaunchKernelGGL(k_conv_fwd<16>, dim3(cdiv(M, kBM), cdiv(c.cout, kBN)), dim3(256), 0, s, c, x, w_nk, b, y);
-    else
-        hipLaunchKernelGGL(k_conv_fwd<32>, dim3(cdiv(M, kBM), cdiv(c.cout, kBN)), dim3(256), 0, s, c, x, w_nk, b, y);
+    if (conv_gather_fits(c, false)) return launch_conv_gather_fwd(c, x, w_nk, b, y, s);
+    if (conv_narrow_fits(c)) return launch_conv_narrow_fwd(c, x, w_nk, b, y, s);
+    hipLaunchKernelGGL(k_conv_fwd, dim3(cdiv(M, kBM), cdiv(c.cout, kBN)), dim3(256), 0, s, c, x, w_nk, b, y);
     UPS_CHECK_HIP(hipGetLastError());
     return UPS_OK;
 }
@@ -326,6 +309,7 @@ ups_status launch_conv_bwd_data(const ConvShape &c, const uint16_t *y, const flo
                                 float *dx, hipStream_t s) {
     const int M = c.n * c.h * c.w;
     if (M == 0) return UPS_OK;
+    if (conv_gather_fits(c, true)) return launch_conv_gather_bwd_data(c, y, dy, w_kn, dx, s);
     hipLaunchKernelGGL(k_conv_bwd_data, dim3(cdiv(M, kBM), cdiv(c.cin, kBN)), dim3(256), 0, s, c, y, dy, w_kn, dx);
     UPS_CHECK_HIP(hipGetLastError());
     return UPS_OK;

@@ -19,67 +19,12 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 struct WgradArgs {
-    ConvShape c;
+    WalkArgs walk;
     const uint16_t *x, *y;
     const float *dy;
     float *part;  // [split][9 cin + 1][cout]
     int chunk;    // output pixels of a split
-    // a step of `unit` output pixels in mixed radix (images, rows, columns)
-    // and what it adds to the centre offset; a wrap to the next row or image
-    int step_oy, step_ox;
-    uint32_t step_add, row_add, image_add;
 };
-
-// An output pixel (oy, ox) of some image and the offset in x of its window's
-// centre, moved along without divisions (which cost more than the rest of
-// the staging: the blocks are bound by its instructions, not by memory).
-struct PixelWalk {
-    int oy, ox;
-    uint32_t centre;
-    __device__ __forceinline__ void start(const ConvShape &c, int p) {
-        const int b = p / (c.ho * c.wo), q = p - b * c.ho * c.wo;
-        oy = q / c.wo, ox = q - oy * c.wo;
-        centre = (uint32_t)((b * c.h + c.stride * oy) * c.w + c.stride * ox) * (uint32_t)c.cin;
-    }
-    __device__ __forceinline__ void wrap(const WgradArgs &a) {
-        if (ox >= a.c.wo) ox -= a.c.wo, oy++, centre += a.row_add;
-        if (oy >= a.c.ho) oy -= a.c.ho, centre += a.image_add;
-    }
-    __device__ __forceinline__ void step(const WgradArgs &a) {
-        ox += a.step_ox, oy += a.step_oy, centre += a.step_add;
-        wrap(a);
-    }
-    __device__ __forceinline__ void next(const WgradArgs &a) {
-        ox++, centre += a.c.stride * a.c.cin;
-        wrap(a);
-    }
-};
-
-// Where tap (ky, kx) of a window lies: `off` from the centre, `wrap_add` more
-// on output column `wrap_ox` (the width is circular), nowhere on output row
-// `no_oy` (the height is zero-padded).
-struct Tap {
-    int off, wrap_add, wrap_ox, no_oy;
-    __device__ __forceinline__ Tap(const ConvShape &c, int ky, int kx) {
-        off = ((ky - 1) * c.w + kx - 1) * c.cin;
-        wrap_add = kx == 0 ? c.w * c.cin : -c.w * c.cin;
-        wrap_ox = kx == 0 ? 0 : (kx == 2 && c.stride * (c.wo - 1) + 1 == c.w) ? c.wo - 1 : -1;
-        no_oy = ky == 0 ? 0 : (ky == 2 && c.stride * (c.ho - 1) + 1 >= c.h) ? c.ho - 1 : -1;
-    }
-    __device__ __forceinline__ bool inside(const PixelWalk &w) const { return w.oy != no_oy; }
-    __device__ __forceinline__ uint32_t at(const PixelWalk &w) const {
-        return w.centre + off + (w.ox == wrap_ox ? wrap_add : 0);
-    }
-};
-
-// Four masked gradients in bfloat16: dy where y > 0.
-__device__ __forceinline__ uint2 masked_grad4(uint2 y, float4 g) {
-    const uint2 h = bf16x4_of(g);
-    auto keep = [](uint32_t y2, uint32_t h2) {  // y as a signed integer is positive where it is not a zero and has no sign
-        return ((int)(y2 << 16) > 0 ? h2 & 0xFFFFu : 0) | ((int)y2 > 0xFFFF ? h2 & 0xFFFF0000u : 0);
-    };
-    return make_uint2(keep(y.x, h.x), keep(y.y, h.y));
-}
 
 // Fragment of rows e0 .. e0+15 over the 32 pixels from p0 of an LDS image
 // [pixel][element] of `pitch` bytes.  Element order of the contraction: lane
@@ -113,7 +58,7 @@ __global__ __launch_bounds__(kWideThreads) void k_conv_wgrad(WgradArgs a) {
     constexpr int kGP = (NF % 2) ? NF * 32 + 64 : NF * 32 + 32;  // an odd multiple of 32 bytes
     __shared__ __align__(16) uint8_t xs[2][kPix * kXP];
     __shared__ __align__(16) uint8_t gs[2][kPix * kGP];
-    const ConvShape &c = a.c;
+    const ConvShape &c = a.walk.c;
     // the wavefront's number as a scalar: MFMA ignores the execution mask, so what it guards has to be a scalar branch
     const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
     const int rows = 9 * c.cin, row0 = blockIdx.x * kRowTile, co0 = blockIdx.y * NF * 16;
@@ -152,9 +97,9 @@ __global__ __launch_bounds__(kWideThreads) void k_conv_wgrad(WgradArgs a) {
                     }
                 f.x[i] = make_uint4(v[0], v[1], v[2], v[3]);
             }
-            if (i < 3) w.next(a);
+            if (i < 3) w.next(a.walk);
         }
-        px.step(a);
+        px.step(a.walk);
         if (gp < kPix)
 #pragma unroll
             for (int hh = 0; hh < 2; hh++) {
@@ -241,7 +186,7 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_conv_wgrad_narrow(WgradAr
     constexpr int kP = 96;                // bytes per pixel: 32 elements, an odd multiple of 32
     constexpr int kWaveBytes = 64 * kP;   // 32 pixels of x, 32 of the gradient
     __shared__ __align__(16) uint8_t lds[kNarrowWaves * kWaveBytes];
-    const ConvShape &c = a.c;
+    const ConvShape &c = a.walk.c;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     uint8_t *xs = lds + wave * kWaveBytes, *gs = xs + 32 * kP;
     constexpr int rows = 9 * CIN;
@@ -270,7 +215,7 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_conv_wgrad_narrow(WgradAr
                 for (int e = 0; e < CIN; e++) xv[k][e] = on ? a.x[at.at(w) + e] : 0;
             }
         }
-        w.step(a);
+        w.step(a.walk);
 #pragma unroll
         for (int k = 0; k < 4; k++) {
             const int pg = p0 + (lane >> 3) + 8 * k, co = co0 + 4 * (lane & 7);
@@ -381,8 +326,8 @@ int max_splits(const ConvShape &c) {
 
 template <int NF>
 void launch_wide(const WgradArgs &a, dim3 grid, hipStream_t s) {
-    if (a.c.cin % 8 == 0) hipLaunchKernelGGL((k_conv_wgrad<NF, 8>), grid, dim3(kWideThreads), 0, s, a);
-    else if (a.c.cin % 2 == 0) hipLaunchKernelGGL((k_conv_wgrad<NF, 2>), grid, dim3(kWideThreads), 0, s, a);
+    if (a.walk.c.cin % 8 == 0) hipLaunchKernelGGL((k_conv_wgrad<NF, 8>), grid, dim3(kWideThreads), 0, s, a);
+    else if (a.walk.c.cin % 2 == 0) hipLaunchKernelGGL((k_conv_wgrad<NF, 2>), grid, dim3(kWideThreads), 0, s, a);
     else hipLaunchKernelGGL((k_conv_wgrad<NF, 1>), grid, dim3(kWideThreads), 0, s, a);
 }
 
@@ -396,19 +341,14 @@ ups_status launch_conv_bwd_weight(const ConvShape &c, const uint16_t *x, const u
     UPS_REQUIRE(conv_wgt_work_floats(c) <= work_floats, "weight-gradient workspace too small");
     int splits = 0;
     if (P > 0) {
-        WgradArgs a{c, x, y, dy, work, 0, 0, 0, 0, 0, 0};
         const bool narrow = c.cin <= 3;
         const int unit = narrow ? 32 * kNarrowWaves : kPix, row_tiles = narrow ? 1 : cdiv(9 * c.cin, kRowTile);
         // 64 channels a block: half the staged windows of 32 for the same products (batch 256, 32 -> 64 and 64 -> 96
         // channels: 25.7 and 26.6 us against 36.0 and 36.9); 32 where there are no more
         const int nf = narrow || c.cout <= 32 ? 2 : 4;
-        a.chunk = cdiv(cdiv(P, max_splits(c)), unit) * unit;
-        splits = cdiv(P, a.chunk);
-        const int s_oy = unit / c.wo % c.ho, s_b = unit / (c.ho * c.wo);
-        a.step_oy = s_oy, a.step_ox = unit % c.wo;
-        a.step_add = ((uint32_t)(s_b * c.h + c.stride * s_oy) * c.w + c.stride * a.step_ox) * (uint32_t)c.cin;
-        a.row_add = (uint32_t)(c.stride * (c.w - c.wo)) * (uint32_t)c.cin;
-        a.image_add = (uint32_t)((c.h - c.stride * c.ho) * c.w) * (uint32_t)c.cin;
+        const int chunk = cdiv(cdiv(P, max_splits(c)), unit) * unit;
+        const WgradArgs a{walk_args(c, unit), x, y, dy, work, chunk};
+        splits = cdiv(P, chunk);
         const dim3 grid(row_tiles, cdiv(c.cout, 16 * nf), splits);
         if (c.cin == 1) hipLaunchKernelGGL(k_conv_wgrad_narrow<1>, grid, dim3(64 * kNarrowWaves), 0, s, a);
         else if (c.cin == 2) hipLaunchKernelGGL(k_conv_wgrad_narrow<2>, grid, dim3(64 * kNarrowWaves), 0, s, a);

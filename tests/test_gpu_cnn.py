@@ -106,6 +106,35 @@ def test_conv_weight_gradient_tile_edges(gpu_lib, shape):
     assert (np.abs(_np(db) - db_ref) <= bound * db_abs).all(), np.abs(_np(db) - db_ref).max()
 
 
+# the forward pass and the data gradient: channel counts in eights (partial 32-channel chunks; more weights than LDS
+# holds at once), output channels past a tile's end, pixel counts around the tiles, odd heights at stride 2 (one odd row
+# fewer), widths of one output pixel, more than 128 output channels at stride 2, at most three input channels
+GATHER_SHAPES = [(1, 1, 2, 8, 4, 2), (1, 5, 8, 40, 24, 2), (3, 7, 34, 24, 36, 2), (2, 3, 9, 136, 20, 1),
+                 (1, 4, 18, 264, 32, 1), (1, 6, 20, 16, 136, 2), (2, 9, 30, 6, 104, 2), (5, 3, 14, 33, 8, 1),
+                 (40, 16, 66, 32, 64, 2), (24, 32, 64, 8, 40, 1), (33, 9, 62, 64, 96, 2), (1, 2, 2, 1, 4, 1),
+                 (3, 5, 22, 3, 44, 1), (2, 16, 40, 2, 36, 2)]
+
+
+@pytest.mark.parametrize("shape", GATHER_SHAPES, ids=[f"n{s[0]}_{s[1]}x{s[2]}_{s[3]}to{s[4]}_s{s[5]}" for s in GATHER_SHAPES])
+def test_conv_gather_tile_edges(gpu_lib, shape):
+    """Forward outputs equal the oracle's rounded to bfloat16 except within the FP32 accumulation bound K 2^-24 sum |x w|
+    of a rounding boundary; input gradients within that bound of their own K terms."""
+    n, h, w, cin, cout, s = shape
+    x, W, b = _layer_case(shape, 600 + h + cin)
+    r = _rng(700 + cout)
+    z = C.conv_forward(x, W, b, s)
+    err = (9 * cin + 1) * EPS32 * (C.conv_forward(np.abs(x), np.abs(W), np.abs(b), s) + 1e-30)
+    y, ref = _np(gpu_lib.conv3x3_forward(_bf(x), _bf(W.T), _f32(b), cout, s)), C.bf16_round(C.relu(z))
+    diff = y != ref
+    assert not (diff & ~_bf16_flip_band(z, err)).any(), int(diff.sum())
+    assert (np.abs(y - ref)[diff] <= 2.0 ** (np.floor(np.log2(np.maximum(np.abs(ref[diff]), 1e-38))) - 7) + err[diff]).all()
+    dy = C.bf16_round(r.normal(size=ref.shape))
+    dx_ref, _, _ = C.conv_backward(x, ref, dy, W, s)
+    dx_abs, _, _ = C.conv_backward(x, ref, np.abs(dy), np.abs(W), s)
+    dx = _np(gpu_lib.conv3x3_backward_data(_bf(ref), _f32(dy), _bf(W), h, w, cin, s))
+    assert (np.abs(dx - dx_ref) <= 9 * cout * EPS32 * dx_abs).all(), np.abs(dx - dx_ref).max()
+
+
 def test_conv_empty_batch(gpu_lib):
     import torch
     x = torch.zeros((0, 8, 16, 4), dtype=torch.bfloat16, device="cuda")
