@@ -117,7 +117,8 @@ __device__ __forceinline__ uint2 masked_grad4(uint2 y, float4 g) {
 
 ConvShape conv_shape(int n, int h, int w, int cin, int cout, int stride);
 ups_status conv_check(const ConvShape &c);
-int64_t conv_wgt_work_floats(const ConvShape &c);
+int64_t conv_wgt_work_floats(const ConvShape &c);  // of this shape
+int64_t conv_wgt_work_limit(const ConvShape &c);   // of this one with any number of images up to its own
 ups_status launch_conv_fwd(const ConvShape &c, const uint16_t *x, const uint16_t *w_nk, const float *b, uint16_t *y,
                            hipStream_t s);
 ups_status launch_conv_bwd_data(const ConvShape &c, const uint16_t *y, const float *dy, const uint16_t *w_kn,
@@ -137,11 +138,29 @@ ups_status launch_conv_bwd_weight(const ConvShape &c, const uint16_t *x, const u
                                   float *dw, float *db, float *work, int64_t work_floats, hipStream_t s);
 ups_status launch_fc_fwd(int n, int feat, const uint16_t *f, const float *Wfc, const float *bfc, float *out,
                          hipStream_t s);
-ups_status launch_loss(int n, const float *y, const float *target, float *dout, float *loss, hipStream_t s);
-ups_status launch_fc_bwd(int n, int feat, const uint16_t *f, const float *dout, const float *Wfc, float *dWfc,
-                         float *dbfc, float *df, hipStream_t s);
-ups_status launch_adam(int64_t n, float *p, const float *g, float *m, float *v, float lr, int64_t step,
-                       hipStream_t s);
+ups_status launch_head_bwd(int n, int feat, const uint16_t *f, const float *y, const float *target, const float *Wfc,
+                           float *dWfc, float *dbfc, float *df, float *loss, hipStream_t s);
+
+// A run of consecutive parameters in an update: a convolution's weights
+// [9 cin][N] and bias [N], whose gradients are the sums of `splits` partial
+// ones, or (sums null) parameters whose gradients are there already.
+struct UpdatePart {
+    int64_t offset, n;
+    int N, splits, block0;
+    const float *sums;
+    uint16_t *w_kn, *w_nk;
+};
+struct UpdateArgs {
+    UpdatePart part[6];
+    int count;
+    float *p, *g, *m, *v;
+    float lr, beta1, beta2, eps, c1, c2;
+};
+// The splits' partial sums of the weight gradient into `work`
+// (conv_wgt_work_floats), and their number; then the update they enter.
+ups_status launch_conv_wgrad_sums(const ConvShape &c, const uint16_t *x, const uint16_t *y, const float *dy, float *work,
+                                  int *splits, hipStream_t s);
+ups_status launch_conv_update(UpdateArgs &a, float lr, int64_t step, hipStream_t s);
 ups_status launch_pack_weight(int K, int N, const float *W, uint16_t *w_kn, uint16_t *w_nk, hipStream_t s);
 
 }  // namespace ups

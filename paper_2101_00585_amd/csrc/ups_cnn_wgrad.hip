@@ -283,20 +283,18 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_conv_wgrad_narrow(WgradAr
     }
 }
 
-// dW and db: the splits' sums added in a fixed order.  A block owns 64 groups
-// of four outputs; its sixteen wavefronts each add every sixteenth split, so
-// that many loads of the latency-bound column are in flight, then the
-// sixteen sums are added in order.
+// The splits' sums of output quad q (four consecutive of the count outputs)
+// added in a fixed order: a block owns 64 quads; its sixteen wavefronts each
+// add every sixteenth split, so that many loads of the latency-bound column
+// are in flight, then the sixteen sums are added in order.  The first
+// wavefront has the result.
 constexpr int kReduceThreads = 1024;
 
-__global__ __launch_bounds__(kReduceThreads) void k_conv_wgrad_reduce(int M, int N, int splits,
-                                                                      const float *__restrict__ part,
-                                                                      float *__restrict__ dw, float *__restrict__ db) {
-    __shared__ float4 red[16][64];
+__device__ __forceinline__ float4 sum_splits(const float *part, int64_t count, int splits, int64_t q, bool on,
+                                             float4 (*red)[64]) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t q = (int64_t)blockIdx.x * 64 + lane, count = (int64_t)M * N, total = count / 4;  // N is a multiple of 4
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (q < total)
+    if (on)
 #pragma unroll 4
         for (int z = wave; z < splits; z += 16) {
             const float4 v = load_f4(part + z * count + 4 * q);
@@ -304,24 +302,80 @@ __global__ __launch_bounds__(kReduceThreads) void k_conv_wgrad_reduce(int M, int
         }
     red[wave][lane] = s;
     __syncthreads();
-    if (wave != 0 || q >= total) return;
+    if (wave == 0)
 #pragma unroll
-    for (int w = 1; w < 16; w++) {
-        const float4 v = red[w][lane];
-        s.x += v.x, s.y += v.y, s.z += v.z, s.w += v.w;
-    }
-    const int64_t i = 4 * q, last = (int64_t)(M - 1) * N;
+        for (int w = 1; w < 16; w++) {
+            const float4 v = red[w][lane];
+            s.x += v.x, s.y += v.y, s.z += v.z, s.w += v.w;
+        }
+    return s;
+}
+
+__global__ __launch_bounds__(kReduceThreads) void k_conv_wgrad_reduce(int M, int N, int splits,
+                                                                      const float *__restrict__ part,
+                                                                      float *__restrict__ dw, float *__restrict__ db) {
+    __shared__ float4 red[16][64];
+    const int64_t q = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63), count = (int64_t)M * N;  // N is a multiple of 4
+    const float4 s = sum_splits(part, count, splits, q, 4 * q < count, red);
+    if (threadIdx.x >= 64 || 4 * q >= count) return;
+    const int64_t i = 4 * q, last = count - N;
     float *o = i < last ? dw + i : db + (i - last);
     o[0] = s.x, o[1] = s.y, o[2] = s.z, o[3] = s.w;
 }
 
+// The whole parameter update of a training step in one launch: the layers'
+// gradients from their splits' sums, Adam (Kingma and Ba) with c1 = 1 / (1 -
+// beta1^t) and c2 = 1 / (1 - beta2^t), and the bfloat16 copies of the
+// convolutions' weights.  As five reductions, Adam and five copies it took
+// 25 + 5.1 + 21 us for the sums of 256 pairs and eleven launches; 19 us so, for 60 MB
+// of sums.
+__global__ __launch_bounds__(kReduceThreads) void k_conv_update(UpdateArgs a) {
+    __shared__ float4 red[16][64];
+    const int lane = threadIdx.x & 63;
+    int l = 0;
+    while (l + 1 < a.count && (int)blockIdx.x >= a.part[l + 1].block0) l++;
+    const UpdatePart &p = a.part[l];
+    const int64_t q = (int64_t)(blockIdx.x - p.block0) * 64 + lane, i0 = 4 * q;
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (p.sums) s = sum_splits(p.sums, p.n, p.splits, q, i0 < p.n, red);
+    if (threadIdx.x >= 64 || i0 >= p.n) return;
+    uint16_t h[4];
+    const int live = (int)min((int64_t)4, p.n - i0);
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+        if (e >= live) break;
+        const int64_t i = p.offset + i0 + e;
+        const float g = p.sums ? (&s.x)[e] : a.g[i];
+        if (p.sums) a.g[i] = g;
+        // written out, so that the rounding does not depend on what the compiler contracts
+        const float mi = fmaf(1.f - a.beta1, g, a.beta1 * a.m[i]);
+        const float vi = fmaf((1.f - a.beta2) * g, g, a.beta2 * a.v[i]);
+        a.m[i] = mi;
+        a.v[i] = vi;
+        const float w = a.p[i] - a.lr * (mi * a.c1) / (sqrtf(vi * a.c2) + a.eps);
+        a.p[i] = w;
+        h[e] = f2bf(w);
+    }
+    const int64_t weights = p.n - p.N;  // the last row is the bias
+    if (!p.w_kn || i0 >= weights) return;
+    const int k = (int)(i0 / p.N), n = (int)(i0 - (int64_t)k * p.N), K = (int)(weights / p.N);
+    *(PackedU2 *)(p.w_kn + i0) = PackedU2{h[0] | (uint32_t)h[1] << 16, h[2] | (uint32_t)h[3] << 16};
+#pragma unroll
+    for (int e = 0; e < 4; e++) p.w_nk[(size_t)(n + e) * K + k] = h[e];
+}
+
 int cdiv(int a, int b) { return (a + b - 1) / b; }
 
-// The most splits of the pixels whose partial sums the workspace holds.
-int max_splits(const ConvShape &c) {
+// Splits of the pixels: about 1024 of the 64 x 64 tiles that the workspace's
+// size was laid out for, at least 64 pixels each.  split_limit: the most that
+// a layer of these channels takes for any number of images up to c.n.
+int split_limit(const ConvShape &c) {
     const int tiles = cdiv(9 * c.cin + 1, 64) * cdiv(c.cout, 64), P = std::max(c.n * c.ho * c.wo, 1);
-    const int splits = std::max(1, std::min(256, cdiv(1024, tiles)));
-    return cdiv(P, std::max(64, cdiv(cdiv(P, splits), 16) * 16));
+    return std::min(std::max(1, std::min(256, cdiv(1024, tiles))), cdiv(P, 64));
+}
+int max_splits(const ConvShape &c) {
+    const int P = std::max(c.n * c.ho * c.wo, 1);
+    return cdiv(P, std::max(64, cdiv(cdiv(P, split_limit(c)), 16) * 16));
 }
 
 template <int NF>
@@ -333,32 +387,56 @@ void launch_wide(const WgradArgs &a, dim3 grid, hipStream_t s) {
 
 }  // namespace
 
+int64_t conv_wgt_work_limit(const ConvShape &c) { return (int64_t)split_limit(c) * (9 * c.cin + 1) * c.cout; }
 int64_t conv_wgt_work_floats(const ConvShape &c) { return (int64_t)max_splits(c) * (9 * c.cin + 1) * c.cout; }
+
+ups_status launch_conv_wgrad_sums(const ConvShape &c, const uint16_t *x, const uint16_t *y, const float *dy, float *work,
+                                  int *splits, hipStream_t s) {
+    const int P = c.n * c.ho * c.wo;
+    *splits = 0;
+    if (P == 0) return UPS_OK;
+    const bool narrow = c.cin <= 3;
+    const int unit = narrow ? 32 * kNarrowWaves : kPix, row_tiles = narrow ? 1 : cdiv(9 * c.cin, kRowTile);
+    // 64 channels a block: half the staged windows of 32 for the same products (batch 256, 32 -> 64 and 64 -> 96
+    // channels: 25.7 and 26.6 us against 36.0 and 36.9); 32 where there are no more
+    const int nf = narrow || c.cout <= 32 ? 2 : 4;
+    const int chunk = cdiv(cdiv(P, max_splits(c)), unit) * unit;
+    const WgradArgs a{walk_args(c, unit), x, y, dy, work, chunk};
+    *splits = cdiv(P, chunk);
+    const dim3 grid(row_tiles, cdiv(c.cout, 16 * nf), *splits);
+    if (c.cin == 1) hipLaunchKernelGGL(k_conv_wgrad_narrow<1>, grid, dim3(64 * kNarrowWaves), 0, s, a);
+    else if (c.cin == 2) hipLaunchKernelGGL(k_conv_wgrad_narrow<2>, grid, dim3(64 * kNarrowWaves), 0, s, a);
+    else if (c.cin == 3) hipLaunchKernelGGL(k_conv_wgrad_narrow<3>, grid, dim3(64 * kNarrowWaves), 0, s, a);
+    else if (nf == 2) launch_wide<2>(a, grid, s);
+    else launch_wide<4>(a, grid, s);
+    UPS_CHECK_HIP(hipGetLastError());
+    return UPS_OK;
+}
 
 ups_status launch_conv_bwd_weight(const ConvShape &c, const uint16_t *x, const uint16_t *y, const float *dy,
                                   float *dw, float *db, float *work, int64_t work_floats, hipStream_t s) {
-    const int M = 9 * c.cin + 1, P = c.n * c.ho * c.wo;
+    const int M = 9 * c.cin + 1;
     UPS_REQUIRE(conv_wgt_work_floats(c) <= work_floats, "weight-gradient workspace too small");
     int splits = 0;
-    if (P > 0) {
-        const bool narrow = c.cin <= 3;
-        const int unit = narrow ? 32 * kNarrowWaves : kPix, row_tiles = narrow ? 1 : cdiv(9 * c.cin, kRowTile);
-        // 64 channels a block: half the staged windows of 32 for the same products (batch 256, 32 -> 64 and 64 -> 96
-        // channels: 25.7 and 26.6 us against 36.0 and 36.9); 32 where there are no more
-        const int nf = narrow || c.cout <= 32 ? 2 : 4;
-        const int chunk = cdiv(cdiv(P, max_splits(c)), unit) * unit;
-        const WgradArgs a{walk_args(c, unit), x, y, dy, work, chunk};
-        splits = cdiv(P, chunk);
-        const dim3 grid(row_tiles, cdiv(c.cout, 16 * nf), splits);
-        if (c.cin == 1) hipLaunchKernelGGL(k_conv_wgrad_narrow<1>, grid, dim3(64 * kNarrowWaves), 0, s, a);
-        else if (c.cin == 2) hipLaunchKernelGGL(k_conv_wgrad_narrow<2>, grid, dim3(64 * kNarrowWaves), 0, s, a);
-        else if (c.cin == 3) hipLaunchKernelGGL(k_conv_wgrad_narrow<3>, grid, dim3(64 * kNarrowWaves), 0, s, a);
-        else if (nf == 2) launch_wide<2>(a, grid, s);
-        else launch_wide<4>(a, grid, s);
-        UPS_CHECK_HIP(hipGetLastError());
+    const ups_status st = launch_conv_wgrad_sums(c, x, y, dy, work, &splits, s);
+    if (st != UPS_OK) return st;
+    hipLaunchKernelGGL(k_conv_wgrad_reduce, dim3((unsigned)(((int64_t)M * c.cout / 4 + 63) / 64)), dim3(kReduceThreads),
+                       0, s, M, c.cout, splits, work, dw, db);
+    UPS_CHECK_HIP(hipGetLastError());
+    return UPS_OK;
+}
+
+ups_status launch_conv_update(UpdateArgs &a, float lr, int64_t step, hipStream_t s) {
+    const double b1 = 0.9, b2 = 0.999;
+    a.lr = lr, a.beta1 = (float)b1, a.beta2 = (float)b2, a.eps = 1e-8f;
+    a.c1 = (float)(1.0 / (1.0 - std::pow(b1, (double)step)));
+    a.c2 = (float)(1.0 / (1.0 - std::pow(b2, (double)step)));
+    int blocks = 0;
+    for (int l = 0; l < a.count; l++) {
+        a.part[l].block0 = blocks;
+        blocks += (int)((a.part[l].n + 255) / 256);
     }
-    hipLaunchKernelGGL(k_conv_wgrad_reduce, dim3((unsigned)(((int64_t)M * c.cout / 4 + 63) / 64)), dim3(kReduceThreads), 0, s, M, c.cout,
-                       splits, work, dw, db);
+    hipLaunchKernelGGL(k_conv_update, dim3(blocks), dim3(kReduceThreads), 0, s, a);
     UPS_CHECK_HIP(hipGetLastError());
     return UPS_OK;
 }

@@ -135,9 +135,9 @@ struct ups_proposal {
     uint16_t *act = nullptr;  // input + five activations (bf16)
     float *dact = nullptr;    // gradients of the five activations
     int64_t act_off[kLayers + 1] = {}, dact_off[kLayers + 1] = {};
-    float *out = nullptr, *dout = nullptr;
-    float *work = nullptr;
-    int64_t work_floats = 0;
+    float *out = nullptr;
+    float *work = nullptr;  // weight-gradient sums, each layer its own until the update
+    int64_t work_off[kLayers] = {}, work_floats = 0;
     PropItem *d_items = nullptr;
     int n_items = 0;
 };
@@ -146,8 +146,7 @@ namespace {
 
 void free_prop(ups_proposal *p) {
     for (void *q : {(void *)p->params, (void *)p->grads, (void *)p->m, (void *)p->v, (void *)p->w_kn, (void *)p->w_nk,
-                    (void *)p->act, (void *)p->dact, (void *)p->out, (void *)p->dout, (void *)p->work,
-                    (void *)p->d_items})
+                    (void *)p->act, (void *)p->dact, (void *)p->out, (void *)p->work, (void *)p->d_items})
         (void)hipFree(q);
     delete p;
 }
@@ -211,7 +210,8 @@ ups_status ups_proposal_create(ups_context *ctx, int32_t max_batch, ups_proposal
         const int64_t sz = (int64_t)max_batch * L.h[k + 1] * L.w[k + 1] * kCout[k];
         ao += sz;
         dofs += sz;
-        p->work_floats = std::max(p->work_floats, conv_wgt_work_floats(layer_shape(k, max_batch)));
+        p->work_off[k] = p->work_floats;
+        p->work_floats += conv_wgt_work_limit(layer_shape(k, max_batch));
     }
     hipError_t e = hipSuccess;
     auto alloc = [&](void **ptr, size_t bytes) {
@@ -226,7 +226,6 @@ ups_status ups_proposal_create(ups_context *ctx, int32_t max_batch, ups_proposal
     alloc((void **)&p->act, ao * sizeof(uint16_t));
     alloc((void **)&p->dact, dofs * sizeof(float));
     alloc((void **)&p->out, (size_t)max_batch * kCnnOut * sizeof(float));
-    alloc((void **)&p->dout, (size_t)max_batch * kCnnOut * sizeof(float));
     alloc((void **)&p->work, p->work_floats * sizeof(float));
     alloc((void **)&p->d_items, (size_t)max_batch * sizeof(PropItem));
     if (e == hipSuccess) e = hipMemset(p->params, 0, L.total * sizeof(float));
@@ -471,26 +470,28 @@ ups_status ups_proposal_train_step(ups_proposal *p, int32_t n, const uint16_t *x
     hipStream_t s = (hipStream_t)stream;
     const Layout &L = layout();
     if ((st = forward_impl(p, n, x, p->out, s)) != UPS_OK) return st;
-    if ((st = launch_loss(n, p->out, target_d, p->dout, loss_d, s)) != UPS_OK) return st;
     const uint16_t *feat = p->act + p->act_off[kLayers];
-    if ((st = launch_fc_bwd(n, L.feat, feat, p->dout, p->params + L.fcw_off, p->grads + L.fcw_off,
-                            p->grads + L.fcb_off, p->dact + p->dact_off[kLayers], s)) != UPS_OK)
+    if ((st = launch_head_bwd(n, L.feat, feat, p->out, target_d, p->params + L.fcw_off, p->grads + L.fcw_off,
+                              p->grads + L.fcb_off, p->dact + p->dact_off[kLayers], loss_d, s)) != UPS_OK)
         return st;
+    UpdateArgs u{};
+    u.p = p->params, u.g = p->grads, u.m = p->m, u.v = p->v;
     for (int k = kLayers - 1; k >= 0; k--) {
         const ConvShape c = layer_shape(k, n);
         const uint16_t *in = k == 0 ? x : p->act + p->act_off[k];
         const uint16_t *y = p->act + p->act_off[k + 1];
         const float *dy = p->dact + p->dact_off[k + 1];
-        if ((st = launch_conv_bwd_weight(c, in, y, dy, p->grads + L.w_off[k], p->grads + L.b_off[k], p->work,
-                                         p->work_floats, s)) != UPS_OK)
-            return st;
+        UpdatePart &up = u.part[u.count++];
+        up = UpdatePart{L.w_off[k], (int64_t)(9 * kCin[k] + 1) * kCout[k], kCout[k], 0, 0, p->work + p->work_off[k],
+                        p->w_kn + L.wb_off[k], p->w_nk + L.wb_off[k]};
+        if ((st = launch_conv_wgrad_sums(c, in, y, dy, p->work + p->work_off[k], &up.splits, s)) != UPS_OK) return st;
         if (k > 0 &&
             (st = launch_conv_bwd_data(c, y, dy, p->w_kn + L.wb_off[k], p->dact + p->dact_off[k], s)) != UPS_OK)
             return st;
     }
+    u.part[u.count++] = UpdatePart{L.fcw_off, L.total - L.fcw_off, 0, 0, 0, nullptr, nullptr, nullptr};
     p->step += 1;
-    if ((st = launch_adam(L.total, p->params, p->grads, p->m, p->v, lr, p->step, s)) != UPS_OK) return st;
-    return pack_all(p, s);
+    return launch_conv_update(u, lr, p->step, s);
 }
 
 // ---- layer-level entry points

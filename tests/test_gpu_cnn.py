@@ -443,3 +443,50 @@ def test_training_loop_resumes_exactly(gpu_lib, prop, tmp_path):
         assert np.array_equal(other.get_params(), want)
     finally:
         other.close()
+
+
+@pytest.mark.parametrize("n", [1, 256, 257, 300])
+def test_train_step_head_and_update(gpu_lib, n):
+    """One training step around the head's runs of 256 samples: loss, head
+    gradients and feature gradient from the step's own output and features
+    within the FP32 accumulation bounds; the convolutions' gradients equal the
+    layer entry point's bit for bit; the parameters are Adam's of those
+    gradients with FP32 constants, to 16 ulp of the step and half an ulp."""
+    import torch
+    ctx = gpu_lib.Context(0, max_pixels=1 << 16)
+    prop = gpu_lib.Proposal(ctx, 300)
+    p, x, target, lr = _params(11), _inputs(12, n), _rng(13).normal(size=(n, 6)), 1e-3
+    prop.set_params(p)
+    y = _np(prop.forward(n, _bf(x)))
+    acts = [_bf(x)] + [_bf(prop.activations(k, n)[0]) for k in range(1, 6)]
+    loss = float(prop.train_step(_bf(x), _f32(target), lr)[0])
+    t32 = np.asarray(target, dtype=np.float32).astype(np.float64)
+    g = prop.get_grads()
+    convs, (dWfc, dbfc) = C.unflatten(g)
+    Wfc = C.unflatten(p.astype(np.float32))[1][0]
+    f, d = _np(acts[5]).reshape(n, -1), C.loss_grad(y, t32)
+    assert abs(loss - C.loss(y, t32)) <= (6 * n + 8) * EPS32 * C.loss(y, t32)
+    assert (np.abs(dWfc - d.T @ f) <= (n + 4) * EPS32 * (np.abs(d).T @ f) + 1e-30).all()
+    assert (np.abs(dbfc - d.sum(0)) <= (n + 4) * EPS32 * np.abs(d).sum(0)).all()
+    df = prop.activations(5, n)[1].reshape(n, -1)
+    assert (np.abs(df - d @ Wfc) <= 10 * EPS32 * (np.abs(d) @ np.abs(Wfc))).all()
+    for k, ((dW, db), (_, _, s)) in enumerate(zip(convs, C.LAYERS)):
+        dy = _f32(prop.activations(k + 1, n)[1])
+        got = gpu_lib.conv3x3_backward_weight(acts[k], acts[k + 1], dy, s)
+        assert np.array_equal(_np(got[0]), dW) and np.array_equal(_np(got[1]), db), k
+    g64, one = g.astype(np.float64), np.float32(1)
+    m = np.float64(one - np.float32(0.9)) * g64 / (1 - 0.9)
+    v = np.float64(one - np.float32(0.999)) * g64 * g64 / (1 - 0.999)
+    step = lr * m / (np.sqrt(v) + 1e-8)
+    p32 = p.astype(np.float32).astype(np.float64)
+    bound = 16 * EPS32 * np.abs(step) + EPS32 * np.abs(p32 - step) + 1e-12
+    assert (np.abs(prop.get_params() - (p32 - step)) <= bound).all()
+    # the updated weights' bfloat16 copies serve the next pass
+    convs, _ = C.unflatten(prop.get_params())
+    prop.forward(n, _bf(x))
+    a1, W1, b1 = prop.activations(1, n)[0], convs[0][0], convs[0][1]
+    z = C.conv_forward(x, C.bf16_round(W1), b1, 2)
+    err = 20 * EPS32 * (C.conv_forward(np.abs(x), np.abs(C.bf16_round(W1)), np.abs(b1), 2) + 1e-30)
+    assert not ((a1 != C.bf16_round(C.relu(z))) & ~_bf16_flip_band(z, err)).any()
+    prop.close()
+    ctx.close()
