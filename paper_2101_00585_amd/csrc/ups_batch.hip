@@ -37,6 +37,10 @@ struct ups_batch {
     int *d_tile_start = nullptr;  // [4][n+1]
     unsigned *d_tile_of = nullptr;  // per level, (registration << 16) | tile of each tile (StepArgs::tile_of)
     int64_t tile_of_off[4] = {0, 0, 0, 0};
+    // the main loop's blocks: group[l] tiles of a registration each (0: one)
+    int group[4] = {0, 0, 0, 0}, total_blocks[4] = {0, 0, 0, 0};
+    unsigned *d_block_of = nullptr;  // per level, (registration << 16) | first tile of each block
+    int64_t block_of_off[4] = {0, 0, 0, 0};
     int *d_pre_start = nullptr;   // [n+1]
     float4 *pyr = nullptr;
     RegState *state = nullptr;    // [n][2]
@@ -94,6 +98,7 @@ void free_batch(ups_batch *b) {
     (void)hipFree(b->d_inst);
     (void)hipFree(b->d_tile_start);
     (void)hipFree(b->d_tile_of);
+    (void)hipFree(b->d_block_of);
     (void)hipFree(b->d_pre_start);
     (void)hipFree(b->pyr);
     (void)hipFree(b->state);
@@ -122,6 +127,24 @@ void free_batch(ups_batch *b) {
 int default_k(ups_context *ctx, int64_t npix) {
     const int tuned = autotuned_k(ctx, npix);
     return tuned > 0 ? tuned : 8;
+}
+
+// Tiles that a block of the main loop takes after one prologue (the reduction
+// of its registration's partials, the solve and the update); 0: one, in the
+// form of the kernel that does not look at its registration's flags first
+// (their round trip costs 0.3 us a launch), for launches whose blocks all run
+// at once.  Where six rounds of blocks remain, more tiles a block save
+// prologues and, once most registrations are done, blocks that only leave.
+// 256 uneven registrations, 15488 tiles of level 0, every one active / most of
+// them done: 222 / 38 us with one tile a block, 212 / 33 with two, 222 / 42
+// with four (and 62 us when a done registration's blocks still read its
+// partials).
+int tiles_per_block(int tiles) {
+    constexpr int kResidentBlocks = 1024;  // four on each of 256 CUs
+    if (tiles <= kResidentBlocks) return 0;
+    int g = 1;
+    while (g < 8 && tiles / (2 * g) >= 6 * kResidentBlocks) g *= 2;
+    return g;
 }
 
 // The pyramids a register / grid-search call builds: every image's, or in
@@ -311,6 +334,16 @@ ups_status ups_batch_create(ups_context *ctx, int32_t n, const ups_batch_item *i
                 tile_of.push_back(((unsigned)k << 16) | (unsigned)(t - tile_start[l * (n + 1) + k]));
     }
     alloc((void **)&b->d_tile_of, std::max<size_t>(tile_of.size(), 1) * sizeof(unsigned));
+    std::vector<unsigned> block_of;
+    for (int l = 0; l < 4; l++) {
+        b->group[l] = tiles_per_block(b->total_tiles[l]);
+        b->block_of_off[l] = (int64_t)block_of.size();
+        for (int k = 0; k < n; k++)
+            for (int t = 0; t < (l < L ? hi[k].nblocks[l] : 0); t += std::max(b->group[l], 1))
+                block_of.push_back(((unsigned)k << 16) | (unsigned)t);
+        b->total_blocks[l] = (int)((int64_t)block_of.size() - b->block_of_off[l]);
+    }
+    alloc((void **)&b->d_block_of, std::max<size_t>(block_of.size(), 1) * sizeof(unsigned));
     alloc((void **)&b->d_pre_start, pre_start.size() * sizeof(int));
     alloc((void **)&b->pyr, std::max<int64_t>(pyr_total, 1) * sizeof(float4));
     alloc((void **)&b->state, (size_t)n * 2 * sizeof(RegState));
@@ -404,6 +437,8 @@ ups_status ups_batch_create(ups_context *ctx, int32_t n, const ups_batch_item *i
         e = hipMemcpy(b->d_tile_start, tile_start.data(), tile_start.size() * sizeof(int), hipMemcpyHostToDevice);
     if (e == hipSuccess && !tile_of.empty())
         e = hipMemcpy(b->d_tile_of, tile_of.data(), tile_of.size() * sizeof(unsigned), hipMemcpyHostToDevice);
+    if (e == hipSuccess && !block_of.empty())
+        e = hipMemcpy(b->d_block_of, block_of.data(), block_of.size() * sizeof(unsigned), hipMemcpyHostToDevice);
     if (e == hipSuccess)
         e = hipMemcpy(b->d_pre_start, pre_start.data(), pre_start.size() * sizeof(int), hipMemcpyHostToDevice);
     if (e == hipSuccess)
@@ -450,7 +485,8 @@ ups_status ups_batch_time_iteration(ups_context *ctx, ups_batch *b, int32_t leve
     a.cos_theta = b->p.cos_theta_max;
     a.irls_delta = b->p.irls_delta;
     a.min_inliers = b->p.min_inliers;
-    a.tile_of = b->d_tile_of + b->tile_of_off[level];
+    a.tile_of = b->d_block_of + b->block_of_off[level];
+    a.group = b->group[level];
     ups_status st;
     if ((st = launch_activate_batch(b->d_inst, b->n, s)) != UPS_OK) return st;
     hipEvent_t e0, e1;
@@ -459,11 +495,11 @@ ups_status ups_batch_time_iteration(ups_context *ctx, ups_batch *b, int32_t leve
     // the main loop's (fused) launch, state slot 0 in, no update pending: the
     // same tile work every launch
     st = launch_icp_batch(b->K[level], b->p.precision, MODE_ITER, b->d_inst, b->d_tile_start + level * (b->n + 1),
-                          b->n, a, b->total_tiles[level], s, true);  // warm-up
+                          b->n, a, b->total_blocks[level], s, true);  // warm-up
     hipError_t e = hipEventRecord(e0, s);
     for (int k = 0; k < n_launches && st == UPS_OK && e == hipSuccess; k++)
         st = launch_icp_batch(b->K[level], b->p.precision, MODE_ITER, b->d_inst,
-                              b->d_tile_start + level * (b->n + 1), b->n, a, b->total_tiles[level], s, true);
+                              b->d_tile_start + level * (b->n + 1), b->n, a, b->total_blocks[level], s, true);
     if (e == hipSuccess) e = hipEventRecord(e1, s);
     if (e == hipSuccess) e = hipEventSynchronize(e1);
     float ms = 0.f;
@@ -552,12 +588,13 @@ ups_status register_batch_fused(ups_batch *b, const ups_pose *init_d, ups_icp_re
     for (int l = p.levels - 1; l >= 0; l--) {
         a.level = l;
         a.d_max2 = p.d_max[l] * p.d_max[l];
-        a.tile_of = b->d_tile_of + b->tile_of_off[l];
+        a.tile_of = b->d_block_of + b->block_of_off[l];
+        a.group = b->group[l];
         for (int it = 0; it < p.iters[l]; it++) {
             a.parity = parity;
             a.first_of_level = it == 0;
             if ((st = launch_icp_batch(b->K[l], p.precision, MODE_ITER, b->d_inst, b->d_tile_start + l * (n + 1), n,
-                                       a, b->total_tiles[l], s, true)) != UPS_OK)
+                                       a, b->total_blocks[l], s, true)) != UPS_OK)
                 return st;
             a.prev_level = l;
             parity ^= 1;
@@ -569,8 +606,9 @@ ups_status register_batch_fused(ups_batch *b, const ups_pose *init_d, ups_icp_re
     a.d_max2 = p.d_max[0] * p.d_max[0];
     a.tau2 = a.d_max2;
     a.check_max_iters = (p.stop_update_norm > 0.0 && p.iters[0] > 0);
-    a.tile_of = b->d_tile_of + b->tile_of_off[0];
-    if ((st = launch_icp_batch(b->K[0], p.precision, MODE_EVAL, b->d_inst, b->d_tile_start, n, a, b->total_tiles[0],
+    a.tile_of = b->d_block_of + b->block_of_off[0];
+    a.group = b->group[0];
+    if ((st = launch_icp_batch(b->K[0], p.precision, MODE_EVAL, b->d_inst, b->d_tile_start, n, a, b->total_blocks[0],
                                s, true)) != UPS_OK)
         return st;
     return launch_finish_batch(p.precision, b->d_inst, n, parity ^ 1, results_d, s);

@@ -74,6 +74,10 @@ struct StepArgs {
     // batches: (registration << 16) | tile of each of the level's tiles in tile
     // order (null: found by binary search in the prefix table of tile counts)
     const unsigned *tile_of;
+    // batches, fused launches: 0: a block per tile; else blocks of `group`
+    // tiles (tile_of lists each block's first), which leave early where their
+    // registration is done
+    int group;
 };
 
 // Debug tile order of the iteration / evaluation launches (ups_debug_reverse_tile_order).

@@ -708,9 +708,16 @@ struct IcpShared {
     int job[8];  // persistent scheduler: ticket's registration and tile, last-arriver flag, spare, job (4 words)
 };
 
-template <int K, int PREC, int MODE, bool FUSED, bool WORLD, bool IRLS, bool STRIDED = FUSED, bool COH = false>
-__device__ __forceinline__ void icp_tile(const Inst &I, const StepArgs &a, int tile, IcpShared<AccOf<PREC>> &sh) {
+// MULTI: the block takes the tiles tile .. tile_end-1 after one prologue, each
+// with sums and a partial of its own (the same partials as a block per tile
+// leaves), and a block whose registration has nothing left to do leaves on the
+// state's flags, before it reads any partial.
+template <int K, int PREC, int MODE, bool FUSED, bool WORLD, bool IRLS, bool STRIDED = FUSED, bool COH = false,
+          bool MULTI = false>
+__device__ __forceinline__ void icp_tile(const Inst &I, const StepArgs &a, const int tile,
+                                         IcpShared<AccOf<PREC>> &sh, const int tile_end = 0) {
     static_assert(!COH || (FUSED && MODE == MODE_ITER), "coherent hand-over: fused iterations only");
+    static_assert(!MULTI || (FUSED && !STRIDED && !COH), "several tiles a block: the batch's main loop");
     constexpr int NV = (MODE == MODE_EVAL) ? 31 : 29;  // EVAL adds valid count and truncated cost
     using Acc = AccOf<PREC>;
     const int tid = threadIdx.x;
@@ -720,6 +727,15 @@ __device__ __forceinline__ void icp_tile(const Inst &I, const StepArgs &a, int t
     const double *part_in = I.partials + (size_t)a.parity * I.pstride * kPartialStride;
     double *part_out = I.partials + (size_t)(FUSED ? (a.parity ^ 1) : 0) * I.pstride * kPartialStride;
 
+    if constexpr (MULTI && MODE == MODE_ITER) {
+        // scalar loads (the descriptor is block-uniform, the state the previous launch's)
+        const int UPS_AS_CONST *f = (const int UPS_AS_CONST *)&slot_in->stop;
+        const int stop = f[0], level_active = f[1], pending = f[2];
+        if (!pending && (stop || (!level_active && !a.first_of_level))) {
+            if (tile == 0 && tid < kStateWords) ((uint32_t *)slot_out)[tid] = ((const uint32_t *)slot_in)[tid];
+            return;
+        }
+    }
     [[maybe_unused]] constexpr bool kPh = FUSED && STRIDED;  // phase timestamps: single registrations
     UPS_PHASE_FIRST(kPh, a.seq);
     UPS_PHASE(kPh, tile, a.seq, 0);
@@ -745,7 +761,7 @@ __device__ __forceinline__ void icp_tile(const Inst &I, const StepArgs &a, int t
     };
     // pixels per thread of this tile: K, or fewer for a scheduled tile
     const int KL = (MODE == MODE_SCHED) ? a.kpt : K;
-    const int base = tile * (kBlock * KL);
+    int base = tile * (kBlock * KL);
 
     // ---- issue the independent loads together: the first pair of scan
     // surfels and their ray-table columns, the previous launch's block
@@ -755,19 +771,22 @@ __device__ __forceinline__ void icp_tile(const Inst &I, const StepArgs &a, int t
     // are in flight before the first of them is consumed, and the next pair's
     // scan loads behind them.
     constexpr int P = (K >= 2) ? 2 : 1;
-    const int pw0 = __builtin_amdgcn_readfirstlane(base + (tid & ~63));
+    int pw0 = __builtin_amdgcn_readfirstlane(base + (tid & ~63));
     // column of this thread's pixel; it advances by kBlock mod cols per pixel
     const int col_step = kBlock % sg.cols;
     float4 nx[P];
     float2 na[P];
     int jc[P];
+    auto first_pixels = [&]() {
 #pragma unroll
-    for (int u = 0; u < P; u++) {
-        if (u == 0) jc[u] = (base + tid) % sg.cols;
-        else jc[u] = jc[u - 1] + col_step >= sg.cols ? jc[u - 1] + col_step - sg.cols : jc[u - 1] + col_step;
-        nx[u] = ldg_u(scan, scan_index(base + u * kBlock + tid, pw0 + u * kBlock, jc[u]));
-        na[u] = ldg_u(sg.lut_col, (uint32_t)jc[u] << sg.lshift);
-    }
+        for (int u = 0; u < P; u++) {
+            if (u == 0) jc[u] = (base + tid) % sg.cols;
+            else jc[u] = jc[u - 1] + col_step >= sg.cols ? jc[u - 1] + col_step - sg.cols : jc[u - 1] + col_step;
+            nx[u] = ldg_u(scan, scan_index(base + u * kBlock + tid, pw0 + u * kBlock, jc[u]));
+            na[u] = ldg_u(sg.lut_col, (uint32_t)jc[u] << sg.lshift);
+        }
+    };
+    first_pixels();
     if (!FUSED) {
         if (MODE == MODE_ITER && !slot_in->active) return;  // uniform: the whole block leaves
         if (MODE == MODE_EVAL && slot_in->skip) return;
@@ -818,6 +837,7 @@ __device__ __forceinline__ void icp_tile(const Inst &I, const StepArgs &a, int t
 #pragma unroll
         for (int k = 0; k < 3; k++) Wk.t[k] = (float)I.wt[k];
     }
+    for (int tl = tile;;) {
     ThreadAcc<PREC, NV> acc;
     acc.zero();
     int pw = pw0;
@@ -895,15 +915,27 @@ __device__ __forceinline__ void icp_tile(const Inst &I, const StepArgs &a, int t
     }
 
     UPS_PHASE(kPh, tile, a.seq, 3);
+    if constexpr (MULTI) {
+        // the next tile's first scan surfels are in flight behind this tile's reduction
+        base += kBlock * KL;
+        pw0 = __builtin_amdgcn_readfirstlane(base + (tid & ~63));
+        if (tl + 1 < tile_end) first_pixels();
+    }
     // ---- 2. block partial
     {
         Acc x[NV];
 #pragma unroll
         for (int v = 0; v < NV; v++) x[v] = (Acc)acc.get(v);
         if constexpr (STRIDED && MODE != MODE_SCHED)
-            block_partial_lds<NV, Acc, COH>(x, part_out, I.pstride, tile);
+            block_partial_lds<NV, Acc, COH>(x, part_out, I.pstride, tl);
         else
-            block_partial<NV, Acc, MODE == MODE_SCHED>(x, qbuf, part_out, I.pstride, tile, tot);
+            block_partial<NV, Acc, MODE == MODE_SCHED>(x, qbuf, part_out, I.pstride, tl, tot);
+    }
+    if constexpr (!MULTI) break;
+    else {
+        if (++tl >= tile_end) break;
+        __syncthreads();  // the reduction's buffer is free again
+    }
     }
     UPS_PHASE(kPh, tile, a.seq, 4);
     if (FUSED && tile == 0) {
@@ -920,10 +952,10 @@ __device__ __forceinline__ void icp_tile(const Inst &I, const StepArgs &a, int t
     UPS_PHASE_LAST(kPh, a.seq);
 }
 
-template <int K, int PREC, int MODE, bool FUSED, bool WORLD, bool IRLS, bool STRIDED = FUSED>
-__device__ __forceinline__ void icp_block(const Inst &I, const StepArgs &a, int tile) {
+template <int K, int PREC, int MODE, bool FUSED, bool WORLD, bool IRLS, bool STRIDED = FUSED, bool MULTI = false>
+__device__ __forceinline__ void icp_block(const Inst &I, const StepArgs &a, int tile, int tile_end = 0) {
     __shared__ IcpShared<AccOf<PREC>> sh;
-    icp_tile<K, PREC, MODE, FUSED, WORLD, IRLS, STRIDED>(I, a, tile, sh);
+    icp_tile<K, PREC, MODE, FUSED, WORLD, IRLS, STRIDED, false, MULTI>(I, a, tile, sh, tile_end);
 }
 
 // Workgroups are dealt to the 8 XCDs in turn (workgroup i to XCD i mod 8), and
@@ -1052,15 +1084,19 @@ __global__ __launch_bounds__(kBlock) void k_icp_level_xcd(Inst I, StepArgs a, in
 // load), or by binary search in the level's prefix table of tile counts
 // (tile_start[n] = total blocks; a chain of dependent loads at the head of
 // every block).  FUSED: each block first applies its registration's pending
-// update (the batch's main loop); otherwise slot 0 holds the pose (the
+// update (the batch's main loop; MULTI: and then takes a.group tiles, of which
+// the table names the first); otherwise slot 0 holds the pose (the
 // subset and scheduled paths, timing).
-template <int K, int PREC, int MODE, bool IRLS, bool FUSED>
+template <int K, int PREC, int MODE, bool IRLS, bool FUSED, bool MULTI = false>
 __global__ __launch_bounds__(kBlock) void k_icp_batch(const Inst *__restrict__ insts,
                                                       const int *__restrict__ tile_start, int n, StepArgs a) {
     const int b = xcd_tile(blockIdx.x, gridDim.x, a.reverse_tiles);
     if (a.tile_of) {
         const unsigned v = a.tile_of[b];
-        icp_block<K, PREC, MODE, FUSED, false, IRLS, false>(insts[v >> 16], a, (int)(v & 0xFFFFu));
+        const Inst &I = insts[v >> 16];
+        const int tile = (int)(v & 0xFFFFu);
+        icp_block<K, PREC, MODE, FUSED, false, IRLS, false, MULTI>(I, a, tile,
+                                                                   min(tile + a.group, I.nblocks[a.level]));
         return;
     }
     int lo = 0, hi = n;  // the last k with tile_start[k] <= b
@@ -1069,7 +1105,8 @@ __global__ __launch_bounds__(kBlock) void k_icp_batch(const Inst *__restrict__ i
         if (tile_start[mid] <= b) lo = mid;
         else hi = mid;
     }
-    icp_block<K, PREC, MODE, FUSED, false, IRLS, false>(insts[lo], a, b - tile_start[lo]);
+    icp_block<K, PREC, MODE, FUSED, false, IRLS, false, MULTI>(insts[lo], a, b - tile_start[lo],
+                                                               b - tile_start[lo] + 1);
 }
 
 // A subset of the batch (a Compact list), in the main loop's fused form: a

@@ -385,3 +385,37 @@ def test_pyramids_built_by_normals_give_the_same_results(gpu_lib, bctx, pairs):
     assert np.array_equal(_np(b.register(init)), ref_p)
     b.close()
     ref_b.close()
+
+
+@pytest.mark.parametrize("precision,irls", [(0, 0.0), (0, 0.01), (1, 0.0), (2, 0.0)])
+def test_blocks_of_several_tiles_give_the_same_bytes(gpu_lib, precision, irls):
+    """Main-loop launches past one round of resident blocks (1024) leave early
+    for finished registrations, and past twelve take two tiles a block: the
+    results of batches of 2,149 and of 13,068 level-0 tiles (27, 52 and 128 a
+    registration at one pixel per thread: odd counts leave a block with one tile)
+    equal, byte for byte, those of small batches, whose blocks take one tile each."""
+    import torch
+    sizes = [(54, 128), (52, 256), (64, 512)]
+    pairs = [W.batch_pair(k, base_seed=7100, max_angle=np.radians(6), max_trans=0.4, size=sizes[k % 3]) for k in range(6)]
+    ctx = gpu_lib.Context(0, max_pixels=1 << 16, max_batch=200, max_batch_pixels=200 * 64 * 512)
+    base = []
+    for p in pairs:
+        g = p["geom"]
+        s, k = (gpu_lib.panorama_normals(ctx, g, torch.from_numpy(p[c]).cuda()) for c in ("scan", "kf"))
+        base.append(dict(scan_geom=g, kf_geom=g, scan_surfel=s, kf_surfel=k))
+    prm = gpu_lib.IcpParams(levels=2, iters=(7, 5, 0, 0), stop_update_norm=1e-4, precision=precision, irls_delta=irls)
+    init = torch.stack([gpu_lib.pose_tensor(np.eye(4))] * 190)
+
+    def run(items):
+        b = gpu_lib.Batch(ctx, items, prm, pixels_per_thread=1)
+        out = b.register(init[:len(items)].contiguous()).cpu().numpy()
+        b.close()
+        return out
+
+    small = run(base)  # 414 tiles
+    assert {r["status"] for r in gpu_lib.read_results(torch.from_numpy(small))} <= {0, 1}
+    for n in (32, 190):
+        got = run([base[k % 6] for k in range(n)])
+        for k in range(n):
+            assert np.array_equal(got[k], small[k % 6]), (n, k)
+    ctx.close()
