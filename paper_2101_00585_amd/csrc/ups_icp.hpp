@@ -36,6 +36,7 @@ struct Inst {
     int nblocks[4];               // blocks (tiles) per level
     ups_icp_result *res;          // finish target (or null)
     ups_normal_eq *neq;           // finish target (or null)
+    void *grid_points[4];         // batches: the grid search's table of the keyframe per level, or null
     unsigned int *xsync;          // single registrations: [4][2] ticket and arrival counters of the one-XCD level
                                   // kernel per level (zero between calls; later launches reset them), or null
     // world-frame variant: the state pose is the scan's world pose, wR/wt the
@@ -136,12 +137,15 @@ struct SchedArgs {
 struct GridArgs {
     int level, n_yaw, n_xy, C;
     float xy_step, d_max2, cos_theta;
+    int points;  // the keyframes' tables (Inst::grid_points) serve this level
 };
 
 int pick_k_single(int npix);
-ups_status launch_grid_search(const Inst *insts, const int *tile_start_l, int n, int K, int tiles,
-                              const ups_pose *base, const GridArgs &g, int *scores, ups_pose *best, int *best_score,
-                              hipStream_t s);
+// Bytes of a keyframe's table at the level of geometry kg.
+size_t grid_points_bytes(const DGeom &kg);
+ups_status launch_grid_search(const Inst *insts, const int *tile_start_l, const unsigned *tile_of, int n, int K,
+                              int tiles, const ups_pose *base, const GridArgs &g, int *scores, ups_pose *best,
+                              int *best_score, hipStream_t s);
 ups_status launch_build_pyramids(const Inst *insts, int n, int levels, const int *pix_start, int total_pix,
                                  const uint8_t *need, hipStream_t s);
 ups_status launch_register(const Inst &I, const ups_pose *init, const ups_icp_params &p, hipStream_t s);

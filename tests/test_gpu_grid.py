@@ -177,3 +177,46 @@ def test_scores_around_a_base_pose(gpu_lib, ctx):
         T[:3, 3] = best.cpu().numpy()[k, 9:]
         np.testing.assert_allclose(T, bases[k] @ _candidate(c_best, 4, 3, 0.5), atol=1e-12)
     b.close()
+
+
+@pytest.mark.parametrize("half", [22.5, 44.5, 70.0])
+def test_keyframe_tables_give_the_general_kernels_scores(gpu_lib, half):
+    """The per-yaw kernels read the keyframe from a table of points at levels 1
+    and up, with a projection of their own; the kernel for more than 5 grid cells
+    per axis reads the images and projects as everywhere else.  A 7 x 7 grid
+    holds the candidates of the 3 x 3 and 1 x 1 grids of the same step: equal
+    scores, for a panorama within +-45 deg and ones that reach past it, with
+    holes, bases of any heading (azimuths on both sides of the seam) and points
+    next to the axes."""
+    import torch
+    rng = np.random.Generator(np.random.PCG64(int(half)))
+    rows, cols = 24, 512
+    g = synth.Geom(rows, cols, math.radians(half), math.radians(2 * half) / (rows - 1))
+    ctx = gpu_lib.Context(0, max_pixels=rows * cols, max_batch=4, max_batch_pixels=4 * rows * cols)
+    items, base = [], []
+    for k in range(4):
+        el = g.el_top - g.d_el * np.arange(rows)[:, None]
+        az = 2 * np.pi * np.arange(cols)[None, :] / cols
+        # a 12 x 8 x 5 m box around the sensor, 2 cm noise, a tenth of the returns missing
+        u = np.stack([np.cos(el) * np.cos(az), np.cos(el) * np.sin(az), np.sin(el) + 0 * az], -1)
+        t = np.min(np.where(u > 0, np.array([6, 4, 3.0]), np.array([-6, -4, -2.0])) / np.where(u == 0, 1e-9, u), -1)
+        images = []
+        for _ in range(2):
+            d = t + 0.02 * rng.normal(size=t.shape)
+            d[rng.uniform(size=t.shape) < 0.1] = 0.0
+            images.append(gpu_lib.panorama_normals(ctx, g, torch.from_numpy(d.astype(np.float32)).cuda()))
+        items.append(dict(scan_geom=g, kf_geom=g, scan_surfel=images[0], kf_surfel=images[1]))
+        base.append(gpu_lib.pose_tensor(synth.se3(synth.rot_z(k * np.pi / 2 + (k > 1) * 0.3), [0.1 * k, 0, 0])))
+    b = gpu_lib.Batch(ctx, items, gpu_lib.IcpParams(levels=3, iters=(1, 1, 1, 0)))
+    base = torch.stack(base)
+    for level in (0, 1, 2):
+        def score(n_xy):
+            gp = gpu_lib.GridParams(level=level, n_yaw=12, n_xy=n_xy, xy_step=0.5, d_max=1.0)
+            return b.grid_search(gp, base)[2].cpu().numpy().reshape(4, 12, n_xy, n_xy)
+        full = score(7)
+        assert full.max() > 0.2 * (rows >> level) * (cols >> level)
+        assert np.array_equal(score(3), full[:, :, 2:5, 2:5])
+        assert np.array_equal(score(5), full[:, :, 1:6, 1:6])
+        assert np.array_equal(score(1), full[:, :, 3:4, 3:4])
+    b.close()
+    ctx.close()
