@@ -57,6 +57,12 @@ __device__ __forceinline__ float2 ldg_u(const float2 *p, uint32_t idx) {
     const v2f v = *(const UPS_AS_GLOBAL v2f *)((const UPS_AS_GLOBAL char *)p + (idx << 3));
     return make_float2(v.x, v.y);
 }
+__device__ __forceinline__ float ldg_u(const float *p, uint32_t idx) {
+    return *(const UPS_AS_GLOBAL float *)((const UPS_AS_GLOBAL char *)p + (idx << 2));
+}
+__device__ __forceinline__ void stg_u(float4 *p, uint32_t idx, float4 v) {
+    *(UPS_AS_GLOBAL v4f *)((UPS_AS_GLOBAL char *)p + (idx << 4)) = v4f{v.x, v.y, v.z, v.w};
+}
 // idx must be the same in every lane of the wavefront
 __device__ __forceinline__ float2 lds_uniform(const float2 *p, int idx) {
     const v2f v = ((const UPS_AS_CONST v2f *)p)[idx];

@@ -83,6 +83,45 @@ def test_normals_parity(gpu_lib, ctx, c0, levels, torch_mod):
     assert err.max() < 2e-4 and np.median(err) < 1e-5, (err.max(), np.median(err))
 
 
+@pytest.mark.parametrize("rows", [2, 5, 17, 24])
+def test_normals_tile_edges(gpu_lib, rows):
+    """Images that end inside a tile, of fewer rows than the filter's reach and
+    of one tile's width: against the oracle in one call, and the same bytes from
+    a batch, whose tiles are taller.  A range enters a cross product with a
+    relative rounding of 6e-8 over neighbours at least 1/50 of the range apart
+    (azimuth 0.1 rad and less, elevation 0.03 and more), a few 1e-6 per normal:
+    the bound is that of test_normals_parity, one threshold decision may flip."""
+    import torch
+    rng = np.random.Generator(np.random.PCG64(rows))
+    el_top = math.radians(20.0)
+    for cols in (64, 192):
+        g = synth.Geom(rows, cols, el_top, 2 * el_top / (rows - 1))
+        el = g.el_top - g.d_el * np.arange(rows)[:, None]
+        az = 2 * np.pi * np.arange(cols)[None, :] / cols
+        u = np.stack([np.cos(el) * np.cos(az), np.cos(el) * np.sin(az), np.sin(el) + 0 * az], -1)
+        t = np.min(np.where(u > 0, [6.0, 4.0, 3.0], [-6.0, -4.0, -2.0]) / np.where(u == 0, 1e-9, u), -1)
+        depth = (t + 0.02 * rng.normal(size=t.shape)) * (rng.uniform(size=t.shape) > 0.1)
+        depth = depth.astype(np.float32)
+        ctx = gpu_lib.Context(0, max_pixels=rows * cols, max_batch=2, max_batch_pixels=2 * rows * cols)
+        for levels in (1, 2, 3):
+            one = gpu_lib.panorama_normals(ctx, g, _t(depth), params=gpu_lib.NormalParams(atrous_levels=levels))
+            gs, os_ = _np(one), O.panorama_normals(g, depth, O.NormalParams(atrous_levels=levels))
+            assert np.array_equal(gs[..., 3], os_[..., 3].astype(np.float32))
+            mg, mo = _normal_mask(gs), _normal_mask(os_)
+            assert int((mg != mo).sum()) <= 1 and mo.sum() > rows * cols // 4
+            err = np.linalg.norm((gs - os_)[mg & mo][:, :3], axis=-1)
+            assert err.max() < 2e-4 and np.median(err) < 1e-5, (err.max(), np.median(err))
+            surf = [torch.zeros(rows, cols, 4, device="cuda") for _ in range(2)]
+            b = gpu_lib.Batch(ctx, [dict(scan_geom=g, kf_geom=g, scan_surfel=surf[0], kf_surfel=surf[1],
+                                         scan_depth=_t(depth), kf_depth=_t(depth))],
+                              gpu_lib.IcpParams(levels=1, iters=(1, 0, 0, 0)))
+            b.normals(gpu_lib.NormalParams(atrous_levels=levels))
+            torch.cuda.synchronize()
+            b.close()
+            assert np.array_equal(_np(surf[0]), gs) and np.array_equal(_np(surf[1]), gs)
+        ctx.close()
+
+
 def test_normals_exact_plane(gpu_lib, ctx):
     g = lidar_geom(64, 512, r_max=200.0)
     el = g.el_top - np.arange(g.rows) * g.d_el
