@@ -44,6 +44,7 @@ struct ups_batch {
     int *d_pre_start = nullptr;   // [n+1]
     float4 *pyr = nullptr;
     char *grid_points = nullptr;  // the grid search's keyframe tables of the levels 1 and up
+    int64_t *d_points_off = nullptr;  // [4][n] byte offsets of the tables in it
     bool points_level[4] = {false, false, false, false};  // levels that have them
     RegState *state = nullptr;    // [n][2]
     double *partials = nullptr;   // [n][2][kPartialStride][pstride]
@@ -104,6 +105,7 @@ void free_batch(ups_batch *b) {
     (void)hipFree(b->d_pre_start);
     (void)hipFree(b->pyr);
     (void)hipFree(b->grid_points);
+    (void)hipFree(b->d_points_off);
     (void)hipFree(b->state);
     (void)hipFree(b->partials);
     (void)hipFree(b->d_nimg);
@@ -349,14 +351,19 @@ ups_status ups_batch_create(ups_context *ctx, int32_t n, const ups_batch_item *i
     alloc((void **)&b->d_block_of, std::max<size_t>(block_of.size(), 1) * sizeof(unsigned));
     alloc((void **)&b->d_pre_start, pre_start.size() * sizeof(int));
     alloc((void **)&b->pyr, std::max<int64_t>(pyr_total, 1) * sizeof(float4));
-    size_t points_total = 0;
+    int64_t points_total = 0;
+    std::vector<int64_t> points_off((size_t)4 * n, 0);
     for (int l = 1; l < L; l++) {
         // entries are numbered in 24 bits
         b->points_level[l] = true;
         for (int k = 0; k < n; k++) b->points_level[l] &= grid_points_bytes(hi[k].kg[l]) <= (24ull << 24);
-        for (int k = 0; b->points_level[l] && k < n; k++) points_total += (grid_points_bytes(hi[k].kg[l]) + 15) / 16 * 16;
+        for (int k = 0; b->points_level[l] && k < n; k++) {
+            points_off[(size_t)l * n + k] = points_total;
+            points_total += (int64_t)(grid_points_bytes(hi[k].kg[l]) + 15) / 16 * 16;
+        }
     }
-    alloc((void **)&b->grid_points, points_total);
+    alloc((void **)&b->grid_points, (size_t)points_total);
+    alloc((void **)&b->d_points_off, points_off.size() * sizeof(int64_t));
     alloc((void **)&b->state, (size_t)n * 2 * sizeof(RegState));
     pstride = (int)partial_stride(pstride);
     alloc((void **)&b->partials, (size_t)n * 2 * pstride * kPartialStride * sizeof(double));
@@ -395,14 +402,8 @@ ups_status ups_batch_create(ups_context *ctx, int32_t n, const ups_batch_item *i
         set_error(std::string("batch allocation failed: ") + hipGetErrorString(e));
         return UPS_ERR_HIP;
     }
-    points_total = 0;
     for (int k = 0; k < n; k++) {
         Inst &I = hi[k];
-        for (int l = 1; l < L; l++) {
-            if (!b->points_level[l]) continue;
-            I.grid_points[l] = b->grid_points + points_total;
-            points_total += (grid_points_bytes(I.kg[l]) + 15) / 16 * 16;
-        }
         I.scan[0] = (const float4 *)items[k].scan_surfel_d;
         I.kf[0] = (const float4 *)items[k].kf_surfel_d;
         int64_t os = pyr_off_s[k], ok = pyr_off_k[k];
@@ -438,6 +439,8 @@ ups_status ups_batch_create(ups_context *ctx, int32_t n, const ups_batch_item *i
         alloc((void **)&b->d_ntile_of, ntile_of.size() * sizeof(unsigned));
     }
     if (e == hipSuccess) e = hipMemcpy(b->d_inst, hi.data(), n * sizeof(Inst), hipMemcpyHostToDevice);
+    if (e == hipSuccess)
+        e = hipMemcpy(b->d_points_off, points_off.data(), points_off.size() * sizeof(int64_t), hipMemcpyHostToDevice);
     if (e == hipSuccess) {
         std::vector<Inst> hs(hi);
         for (int k = 0; k < n; k++) {
@@ -785,7 +788,9 @@ ups_status ups_batch_grid_search(ups_context *ctx, ups_batch *b, const ups_grid_
     g.xy_step = gp->xy_step;
     g.d_max2 = gp->d_max * gp->d_max;
     g.cos_theta = gp->cos_theta_max;
-    g.points = b->points_level[l] && gp->n_xy <= 5;  // the general kernel reads the keyframe's images
+    // the general kernel reads the keyframe's images
+    g.points = b->points_level[l] && gp->n_xy <= 5 ? b->grid_points : nullptr;
+    g.points_off = b->d_points_off + (size_t)l * n;
     return launch_grid_search(b->d_inst, b->d_tile_start + l * (n + 1), b->d_tile_of + b->tile_of_off[l], n, b->K[l],
                               b->total_tiles[l], base_d, g, scores_d, best_d, best_score_d, s);
 }

@@ -156,7 +156,7 @@ __global__ __launch_bounds__(kBlock) void k_grid_points(const Inst *__restrict__
     if (!g.points) return;
     const DGeom kg = I.kg[l];
     const int pitch = kg.cols + 1, total = kg.rows * pitch;
-    GridPoint *out = (GridPoint *)I.grid_points[l];
+    GridPoint *out = (GridPoint *)(g.points + g.points_off[blockIdx.y]);
     for (int q = first; q <= total; q += stride) {
         const int i = q / pitch, j = q - i * pitch;
         const float nan = __int_as_float(0x7fc00000);
@@ -207,7 +207,7 @@ __global__ __launch_bounds__(kBlock) void k_grid_score_yaw(const Inst *__restric
     const DGeom sg = I.sg[l], kg = I.kg[l];
     const float4 *__restrict__ scan = I.scan[l];
     const float4 *__restrict__ kf = I.kf[l];
-    const void *points = I.grid_points[l];
+    const char *points = g.points + (POINTS ? g.points_off[reg] : 0);
     const int pitch = kg.cols + 1;
     const uint32_t nowhere = (uint32_t)(kg.rows * pitch);
     const int a0 = chunk * YB;

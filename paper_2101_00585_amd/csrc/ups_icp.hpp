@@ -36,7 +36,6 @@ struct Inst {
     int nblocks[4];               // blocks (tiles) per level
     ups_icp_result *res;          // finish target (or null)
     ups_normal_eq *neq;           // finish target (or null)
-    void *grid_points[4];         // batches: the grid search's table of the keyframe per level, or null
     unsigned int *xsync;          // single registrations: [4][2] ticket and arrival counters of the one-XCD level
                                   // kernel per level (zero between calls; later launches reset them), or null
     // world-frame variant: the state pose is the scan's world pose, wR/wt the
@@ -137,7 +136,8 @@ struct SchedArgs {
 struct GridArgs {
     int level, n_yaw, n_xy, C;
     float xy_step, d_max2, cos_theta;
-    int points;  // the keyframes' tables (Inst::grid_points) serve this level
+    char *points;               // the keyframes' tables, or null where the images are read instead
+    const int64_t *points_off;  // [n] byte offset of each registration's
 };
 
 int pick_k_single(int npix);
