@@ -238,7 +238,9 @@ def _torch():
 
 
 def _stream():
-    return _P(_torch().cuda.current_stream().cuda_stream)
+    # the current stream's handle without a Stream object around it: 0.3 us a call instead of 3.0
+    torch = _torch()
+    return _P(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
 
 def _dev_ptr(t, dtype, what):

@@ -166,3 +166,14 @@ def test_persistent_scheduler_repeats_and_agrees(gpu_lib, ctx):
         print(f"pair {k}: persistent vs oracle {rot:.2e} rad {tr:.2e} m")
         assert rot < 1e-5 and tr < 1e-5
     b.close()
+
+
+def test_calls_go_to_the_current_stream(gpu_lib):
+    """The handle that every entry point is given: the default stream's, an
+    entered stream's, and the default's again."""
+    import torch
+    s = torch.cuda.Stream()
+    assert (gpu_lib._stream().value or 0) == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(s):
+        assert (gpu_lib._stream().value or 0) == s.cuda_stream != 0
+    assert (gpu_lib._stream().value or 0) == torch.cuda.current_stream().cuda_stream
