@@ -68,16 +68,16 @@ struct StepArgs {
     int min_inliers;
     double stop_norm;
     int kpt;  // MODE_SCHED: pixels per thread of this tile (<= the kernel's K, a multiple of its pixel groups)
+    // batches, fused launches: 0: a block per tile; else blocks of `group`
+    // tiles (tile_of lists each block's first), which leave early where their
+    // registration is done
+    int group;
     const ups_pose *init;  // single registrations: the first launch builds the state from this start pose
     int reverse_tiles;  // debug: workgroups take the tiles in reverse order (set by the launchers)
     int seq;            // single registrations: the launch's number within the call (phase timestamps)
     // batches: (registration << 16) | tile of each of the level's tiles in tile
     // order (null: found by binary search in the prefix table of tile counts)
     const unsigned *tile_of;
-    // batches, fused launches: 0: a block per tile; else blocks of `group`
-    // tiles (tile_of lists each block's first), which leave early where their
-    // registration is done
-    int group;
 };
 
 // Debug tile order of the iteration / evaluation launches (ups_debug_reverse_tile_order).
