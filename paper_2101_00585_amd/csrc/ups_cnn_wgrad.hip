@@ -283,31 +283,47 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_conv_wgrad_narrow(WgradAr
     }
 }
 
-// The splits' sums of output quad q (four consecutive of the count outputs)
-// added in a fixed order: a block owns 64 quads; its sixteen wavefronts each
-// add every sixteenth split, so that many loads of the latency-bound column
-// are in flight, then the sixteen sums are added in order.  The first
-// wavefront has the result.
-constexpr int kReduceThreads = 1024;
+// The splits' sums of a block's 64 quads of outputs (four consecutive of the
+// count outputs each), added in a fixed order: sixteen sums, of every
+// sixteenth split, to be added in turn (ordered_sum) after a barrier.  Bound by
+// the latency of the loads: each wavefront makes four of the sixteen sums, two
+// splits of each in flight.
+constexpr int kReduceThreads = 256, kReduceWaves = kReduceThreads / 64, kReduceSums = 16 / kReduceWaves;
+constexpr int kReduceAhead = 2;  // 7 wavefronts a SIMD; 1, 3 and 4: 16.7, 15.7 and 15.5 us for k_conv_update's 15.0
 
-__device__ __forceinline__ float4 sum_splits(const float *part, int64_t count, int splits, int64_t q, bool on,
-                                             float4 (*red)[64]) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (on)
-#pragma unroll 4
-        for (int z = wave; z < splits; z += 16) {
-            const float4 v = load_f4(part + z * count + 4 * q);
-            s.x += v.x, s.y += v.y, s.z += v.z, s.w += v.w;
-        }
-    red[wave][lane] = s;
-    __syncthreads();
-    if (wave == 0)
+__device__ __forceinline__ void sum_splits(const float *part, int64_t count, int splits, int64_t q, bool on,
+                                           float4 (*red)[64]) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    float4 s[kReduceSums];
 #pragma unroll
-        for (int w = 1; w < 16; w++) {
-            const float4 v = red[w][lane];
-            s.x += v.x, s.y += v.y, s.z += v.z, s.w += v.w;
-        }
+    for (int j = 0; j < kReduceSums; j++) s[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+    part += on ? 4 * q : 0;
+    for (int z0 = wave; z0 < splits; z0 += 16 * kReduceAhead) {
+        float4 v[kReduceAhead][kReduceSums];
+#pragma unroll
+        for (int u = 0; u < kReduceAhead; u++)
+#pragma unroll
+            for (int j = 0; j < kReduceSums; j++) {
+                const int z = z0 + 16 * u + kReduceWaves * j;
+                v[u][j] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (z < splits) v[u][j] = load_f4(part + z * count);
+            }
+#pragma unroll
+        for (int u = 0; u < kReduceAhead; u++)
+#pragma unroll
+            for (int j = 0; j < kReduceSums; j++)
+                s[j].x += v[u][j].x, s[j].y += v[u][j].y, s[j].z += v[u][j].z, s[j].w += v[u][j].w;
+    }
+#pragma unroll
+    for (int j = 0; j < kReduceSums; j++) red[wave + kReduceWaves * j][lane] = s[j];
+}
+
+// The block's output threadIdx.x.
+__device__ __forceinline__ float ordered_sum(const float4 (*red)[64]) {
+    const float *r = (const float *)red + threadIdx.x;
+    float s = r[0];
+#pragma unroll
+    for (int w = 1; w < 16; w++) s += r[256 * w];
     return s;
 }
 
@@ -316,52 +332,51 @@ __global__ __launch_bounds__(kReduceThreads) void k_conv_wgrad_reduce(int M, int
                                                                       float *__restrict__ dw, float *__restrict__ db) {
     __shared__ float4 red[16][64];
     const int64_t q = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63), count = (int64_t)M * N;  // N is a multiple of 4
-    const float4 s = sum_splits(part, count, splits, q, 4 * q < count, red);
-    if (threadIdx.x >= 64 || 4 * q >= count) return;
-    const int64_t i = 4 * q, last = count - N;
-    float *o = i < last ? dw + i : db + (i - last);
-    o[0] = s.x, o[1] = s.y, o[2] = s.z, o[3] = s.w;
+    sum_splits(part, count, splits, q, 4 * q < count, red);
+    __syncthreads();
+    const int64_t i = (int64_t)blockIdx.x * kReduceThreads + threadIdx.x, last = count - N;
+    if (i >= count) return;
+    *(i < last ? dw + i : db + (i - last)) = ordered_sum(red);
 }
 
 // The whole parameter update of a training step in one launch: the layers'
 // gradients from their splits' sums, Adam (Kingma and Ba) with c1 = 1 / (1 -
 // beta1^t) and c2 = 1 / (1 - beta2^t), and the bfloat16 copies of the
-// convolutions' weights.  As five reductions, Adam and five copies it took
-// 25 + 5.1 + 21 us for the sums of 256 pairs and eleven launches; 19 us so, for 60 MB
-// of sums.
+// convolutions' weights; a parameter a thread, its moments on their way during
+// the sums.  Blocks of four wavefronts are all resident at once for the
+// network's 360000 parameters: 15.0 us for the 60 MB of sums of 256 pairs, against
+// 18.4 with sixteen wavefronts (2.75 rounds of blocks, the moments after the
+// sums by one wavefront).
 __global__ __launch_bounds__(kReduceThreads) void k_conv_update(UpdateArgs a) {
     __shared__ float4 red[16][64];
-    const int lane = threadIdx.x & 63;
     int l = 0;
     while (l + 1 < a.count && (int)blockIdx.x >= a.part[l + 1].block0) l++;
     const UpdatePart &p = a.part[l];
-    const int64_t q = (int64_t)(blockIdx.x - p.block0) * 64 + lane, i0 = 4 * q;
-    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (p.sums) s = sum_splits(p.sums, p.n, p.splits, q, i0 < p.n, red);
-    if (threadIdx.x >= 64 || i0 >= p.n) return;
-    uint16_t h[4];
-    const int live = (int)min((int64_t)4, p.n - i0);
-#pragma unroll
-    for (int e = 0; e < 4; e++) {
-        if (e >= live) break;
-        const int64_t i = p.offset + i0 + e;
-        const float g = p.sums ? (&s.x)[e] : a.g[i];
-        if (p.sums) a.g[i] = g;
-        // written out, so that the rounding does not depend on what the compiler contracts
-        const float mi = fmaf(1.f - a.beta1, g, a.beta1 * a.m[i]);
-        const float vi = fmaf((1.f - a.beta2) * g, g, a.beta2 * a.v[i]);
-        a.m[i] = mi;
-        a.v[i] = vi;
-        const float w = a.p[i] - a.lr * (mi * a.c1) / (sqrtf(vi * a.c2) + a.eps);
-        a.p[i] = w;
-        h[e] = f2bf(w);
+    const int64_t j = (int64_t)(blockIdx.x - p.block0) * kReduceThreads + threadIdx.x;  // in the part
+    const int64_t i = p.offset + min(j, p.n - 1);
+    float g = p.sums ? 0.f : a.g[i];
+    const float m = a.m[i], v = a.v[i], w0 = a.p[i];
+    if (p.sums) {
+        const int64_t q = (int64_t)(blockIdx.x - p.block0) * 64 + (threadIdx.x & 63);
+        sum_splits(p.sums, p.n, p.splits, q, 4 * q < p.n, red);
+        __syncthreads();
+        g = ordered_sum(red);
     }
+    if (j >= p.n) return;
+    if (p.sums) a.g[i] = g;
+    // written out, so that the rounding does not depend on what the compiler contracts
+    const float mi = fmaf(1.f - a.beta1, g, a.beta1 * m);
+    const float vi = fmaf((1.f - a.beta2) * g, g, a.beta2 * v);
+    a.m[i] = mi;
+    a.v[i] = vi;
+    const float w = w0 - a.lr * (mi * a.c1) / (sqrtf(vi * a.c2) + a.eps);
+    a.p[i] = w;
     const int64_t weights = p.n - p.N;  // the last row is the bias
-    if (!p.w_kn || i0 >= weights) return;
-    const int k = (int)(i0 / p.N), n = (int)(i0 - (int64_t)k * p.N), K = (int)(weights / p.N);
-    *(PackedU2 *)(p.w_kn + i0) = PackedU2{h[0] | (uint32_t)h[1] << 16, h[2] | (uint32_t)h[3] << 16};
-#pragma unroll
-    for (int e = 0; e < 4; e++) p.w_nk[(size_t)(n + e) * K + k] = h[e];
+    if (!p.w_kn || j >= weights) return;
+    const uint16_t h = f2bf(w);
+    const int k = (int)(j / p.N), n = (int)(j - (int64_t)k * p.N), K = (int)(weights / p.N);
+    p.w_kn[j] = h;
+    p.w_nk[(size_t)n * K + k] = h;
 }
 
 int cdiv(int a, int b) { return (a + b - 1) / b; }

@@ -106,6 +106,18 @@ def test_conv_weight_gradient_tile_edges(gpu_lib, shape):
     assert (np.abs(_np(db) - db_ref) <= bound * db_abs).all(), np.abs(_np(db) - db_ref).max()
 
 
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 33, 65, 130])
+def test_conv_weight_gradient_split_counts(gpu_lib, n):
+    """n splits of 64 pixels each, around the sixteen sums and the two splits in
+    flight of the reduction: whole numbers whose sums stay below 2^24, so exact."""
+    r = _rng(800 + n)
+    x = r.integers(0, 4, size=(n, 2, 32, 4)).astype(np.float64)
+    dy = r.integers(-3, 4, size=(n, 2, 32, 60)).astype(np.float64)
+    _, dW_ref, db_ref = C.conv_backward(x, np.ones_like(dy), dy, np.zeros((36, 60)), 1)
+    dW, db = gpu_lib.conv3x3_backward_weight(_bf(x), _bf(np.ones_like(dy)), _f32(dy), 1)
+    assert np.array_equal(_np(dW), dW_ref) and np.array_equal(_np(db), db_ref)
+
+
 # the forward pass and the data gradient: channel counts in eights (partial 32-channel chunks; more weights than LDS
 # holds at once), output channels past a tile's end, pixel counts around the tiles, odd heights at stride 2 (one odd row
 # fewer), widths of one output pixel, more than 128 output channels at stride 2, at most three input channels
