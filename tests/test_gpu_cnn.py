@@ -502,3 +502,13 @@ def test_train_step_head_and_update(gpu_lib, n):
     assert not ((a1 != C.bf16_round(C.relu(z))) & ~_bf16_flip_band(z, err)).any()
     prop.close()
     ctx.close()
+
+
+# two input channels at stride 2 on rows of whole 256-pixel segments: one row, odd heights (a window past the last row),
+# one and several segments a row (the left neighbour across the seam, or in the previous segment), channels past a tile's end, more segments than
+# wavefronts of a full grid
+@pytest.mark.parametrize("shape", [(1, 1, 256, 2, 4, 2), (3, 5, 256, 2, 36, 2), (2, 4, 512, 2, 32, 2), (1, 3, 768, 2, 8, 2),
+                                   (130, 127, 256, 2, 4, 2)],
+                         ids=lambda s: f"n{s[0]}_{s[1]}x{s[2]}_{s[3]}to{s[4]}")
+def test_conv_forward_row_segments(gpu_lib, shape):
+    test_conv_gather_tile_edges(gpu_lib, shape)
