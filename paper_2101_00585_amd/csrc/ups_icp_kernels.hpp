@@ -777,16 +777,13 @@ __device__ __forceinline__ void icp_tile(const Inst &I, const StepArgs &a, const
     float4 nx[P];
     float2 na[P];
     int jc[P];
-    auto first_pixels = [&]() {
 #pragma unroll
-        for (int u = 0; u < P; u++) {
-            if (u == 0) jc[u] = (base + tid) % sg.cols;
-            else jc[u] = jc[u - 1] + col_step >= sg.cols ? jc[u - 1] + col_step - sg.cols : jc[u - 1] + col_step;
-            nx[u] = ldg_u(scan, scan_index(base + u * kBlock + tid, pw0 + u * kBlock, jc[u]));
-            na[u] = ldg_u(sg.lut_col, (uint32_t)jc[u] << sg.lshift);
-        }
-    };
-    first_pixels();
+    for (int u = 0; u < P; u++) {
+        if (u == 0) jc[u] = (base + tid) % sg.cols;
+        else jc[u] = jc[u - 1] + col_step >= sg.cols ? jc[u - 1] + col_step - sg.cols : jc[u - 1] + col_step;
+        nx[u] = ldg_u(scan, scan_index(base + u * kBlock + tid, pw0 + u * kBlock, jc[u]));
+        na[u] = ldg_u(sg.lut_col, (uint32_t)jc[u] << sg.lshift);
+    }
     if (!FUSED) {
         if (MODE == MODE_ITER && !slot_in->active) return;  // uniform: the whole block leaves
         if (MODE == MODE_EVAL && slot_in->skip) return;
@@ -919,7 +916,15 @@ __device__ __forceinline__ void icp_tile(const Inst &I, const StepArgs &a, const
         // the next tile's first scan surfels are in flight behind this tile's reduction
         base += kBlock * KL;
         pw0 = __builtin_amdgcn_readfirstlane(base + (tid & ~63));
-        if (tl + 1 < tile_end) first_pixels();
+        if (tl + 1 < tile_end) {
+#pragma unroll
+            for (int u = 0; u < P; u++) {
+                if (u == 0) jc[u] = (base + tid) % sg.cols;
+                else jc[u] = jc[u - 1] + col_step >= sg.cols ? jc[u - 1] + col_step - sg.cols : jc[u - 1] + col_step;
+                nx[u] = ldg_u(scan, scan_index(base + u * kBlock + tid, pw0 + u * kBlock, jc[u]));
+                na[u] = ldg_u(sg.lut_col, (uint32_t)jc[u] << sg.lshift);
+            }
+        }
     }
     // ---- 2. block partial
     {
