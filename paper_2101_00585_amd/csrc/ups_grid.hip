@@ -188,7 +188,7 @@ __global__ __launch_bounds__(kBlock) void k_grid_points(const Inst *__restrict__
 // chunks that run together.
 // Bound by the vector instructions of a candidate, mostly the two arctangents.
 // POINTS: the keyframe comes from the table of k_grid_points (levels 1 and
-// up): no ray tables, no surfel test, one address: 216 us against 300
+// up): no ray tables, no surfel test, one address: 227 us against 300
 // for 64 registrations x 324 candidates at level 2, with 7.7 us to fill the table.
 template <int NXY, int YB, bool POINTS>
 __global__ __launch_bounds__(kBlock) void k_grid_score_yaw(const Inst *__restrict__ insts,

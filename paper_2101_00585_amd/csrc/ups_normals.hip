@@ -59,9 +59,10 @@ __global__ __launch_bounds__(kBlock) void k_normals_raw(DGeom g, const float *__
 // once for up to five of them.  The passes are bound by vector instructions:
 // 225 a pixel for the taps, the rest for staging, raw normals and ends.
 // Batches take 16 rows, whose halo is the smaller part of a tile: the two
-// passes over 512 panoramas of 64 x 1024 take 275 and 249 us, against 365 and
-// 325 with a row a time per lane and pixels staged one by one (370 and 279
-// instructions a pixel, against 424 and 304).  A single panorama has too few
+// passes over 256 scans of 64 x 512 to 128 x 2048 (31.7 million pixels) take
+// 275 and 249 us, against 365 and 325 with a row a time per lane and pixels
+// staged one by one (370 and 279 instructions a pixel, against 424 and 304).
+// A single panorama has too few
 // rows to fill the chip with that: 4 rows a tile take 4.4 + 3.4 us at 64 x
 // 1024 where 8 take 5.1 + 4.0 and 16 take 6.6 + 5.2, and at 256 x 2048 all
 // lie within 7 % (25.4, 25.0 and 26.7 us for three passes).
