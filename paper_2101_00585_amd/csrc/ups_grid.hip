@@ -46,8 +46,11 @@ __device__ __forceinline__ int floor_int(float v) {
 // (the column is not wrapped), for a panorama that is `NARROW` or not: the
 // same angles, with fewer instructions around them.  The azimuth's sign and
 // turn are one step (2 pi - r where y is negative; a zero r then gives column
-// cols for 0, the same column), the row is tested as an integer (a NaN
-// direction, row 0, is left to the distance test, which it fails).
+// cols for 0, the same column), the row is tested as an integer.  An elevation
+// that is no number (the origin, a point of denormal coordinates) has no pixel.
+// Next to the vertical axis the reciprocal overflows and the column is any
+// integer: callers bound the entry, except where `NARROW`, whose directions
+// have |z| < rho and so an x or y whose square is no zero.
 template <bool NARROW>
 __device__ __forceinline__ bool project_at(const DGeom &g, float3 q, uint32_t pitch, uint32_t &at) {
     const float rho = __builtin_amdgcn_sqrtf(q.x * q.x + q.y * q.y);
@@ -57,8 +60,8 @@ __device__ __forceinline__ bool project_at(const DGeom &g, float3 q, uint32_t pi
         ok = fabsf(q.z) < rho;
         el = atan_unit(q.z * __builtin_amdgcn_rcpf(rho));
     } else {
-        ok = (rho != 0.f) | (q.z != 0.f);
         el = atan2_fast(q.z, rho);
+        ok = el == el;
     }
     const float ax = fabsf(q.x), ay = fabsf(q.y);
     const bool steep = ay > ax;
@@ -270,7 +273,9 @@ __global__ __launch_bounds__(kBlock) void k_grid_score_yaw(const Inst *__restric
                     if constexpr (POINTS) {
                         uint32_t at;
                         const bool ok = project_at<decltype(narrow)::value>(kg, q, (uint32_t)pitch, at) & sok;
-                        at = __umul24(ok ? at : nowhere, 24u);
+                        at = ok ? at : nowhere;
+                        if constexpr (!decltype(narrow)::value) at = min(at, nowhere);
+                        at = __umul24(at, 24u);
                         const UPS_AS_GLOBAL char *gp = (const UPS_AS_GLOBAL char *)points + at;
                         v_of[c & 1] = *(const UPS_AS_GLOBAL v4fa *)gp;
                         w_of[c & 1] = *(const UPS_AS_GLOBAL v2f *)(gp + 16);

@@ -220,3 +220,36 @@ def test_keyframe_tables_give_the_general_kernels_scores(gpu_lib, half):
         assert np.array_equal(score(1), full[:, :, 3:4, 3:4])
     b.close()
     ctx.close()
+
+
+def test_points_of_denormal_range_project_nowhere(gpu_lib):
+    """Surfels whose ranges are denormal are valid where the sensor has no
+    minimum range, and the azimuth and elevation of such a point are no numbers:
+    outside +-45 deg they count for no candidate, with the table as with the
+    images (7 x 7), although a keyframe 0.5 m away lies within reach."""
+    import torch
+    rows, cols = 24, 512
+    g = synth.Geom(rows, cols, math.radians(70.0), math.radians(140.0) / (rows - 1))
+    assert g.r_min == 0.0
+    el = g.el_top - g.d_el * np.arange(rows)[:, None]
+    az = 2 * np.pi * np.arange(cols)[None, :] / cols
+    u = np.stack([np.cos(el) * np.cos(az), np.cos(el) * np.sin(az), np.sin(el) + 0 * az], -1)
+    kf = np.concatenate([-u, np.full(u.shape[:2] + (1,), 0.5)], -1).astype(np.float32)
+    scan = kf.copy()
+    scan[:, ::8, 3] = np.float32(1e-39)  # every second pixel of level 2, the columns of the axes among them
+    assert scan[0, 0, 3] > 0
+    ctx = gpu_lib.Context(0, max_pixels=rows * cols, max_batch=1, max_batch_pixels=rows * cols)
+    b = gpu_lib.Batch(ctx, [dict(scan_geom=g, kf_geom=g, scan_surfel=_t(scan), kf_surfel=_t(kf))],
+                      gpu_lib.IcpParams(levels=3, iters=(1, 1, 1, 0)))
+    base = torch.stack([gpu_lib.pose_tensor(np.eye(4))])
+    for level in (1, 2):
+        def score(n_xy):
+            gp = gpu_lib.GridParams(level=level, n_yaw=12, n_xy=n_xy, xy_step=0.0, d_max=1.0)
+            return b.grid_search(gp, base)[2].cpu().numpy().reshape(12, n_xy, n_xy)
+        full = score(7)
+        usable = np.count_nonzero(scan[::1 << level, ::1 << level, 3] == 0.5)
+        assert (full[0] == usable).all()
+        assert np.array_equal(score(3), full[:, 2:5, 2:5])
+        assert np.array_equal(score(1), full[:, 3:4, 3:4])
+    b.close()
+    ctx.close()
