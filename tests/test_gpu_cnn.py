@@ -31,9 +31,7 @@ def _np(t):
     return t.detach().to(torch.float64).cpu().numpy()
 
 
-# network layers plus shapes with ragged tiles, odd channel counts and stride 1;
-# between them every operand-gather path of the forward pass (four channels
-# per load, channel pairs, single channels) with 16- and 32-wide K slices
+# network layers plus shapes with ragged tiles, odd channel counts and stride 1
 SHAPES = [(2, h, w, cin, cout, s) for (h, w, cin, cout, s) in C.shapes()[0]] + [
     (3, 6, 12, 3, 8, 1), (1, 5, 14, 6, 12, 2), (5, 4, 64, 16, 68, 2), (2, 4, 8, 5, 8, 1), (1, 3, 10, 1, 4, 2)]
 
@@ -145,6 +143,20 @@ def test_conv_gather_tile_edges(gpu_lib, shape):
     dx_abs, _, _ = C.conv_backward(x, ref, np.abs(dy), np.abs(W), s)
     dx = _np(gpu_lib.conv3x3_backward_data(_bf(ref), _f32(dy), _bf(W), h, w, cin, s))
     assert (np.abs(dx - dx_ref) <= 9 * cout * EPS32 * dx_abs).all(), np.abs(dx - dx_ref).max()
+
+
+# launches of many pixels, whose blocks take larger tiles: k_conv_gather<forward, 4, 2, 8, 2> with its weights in one piece
+# and in several, <forward, 2, 2, 8, 4> in several, <gradient, 2, 2, 4, 2> in one piece and in several, and
+# k_conv_bwd_data_s2 for 1, 2 and 3 chunks of output channels; each past its threshold by a partial last block, with
+# channels past a tile's end and, at stride 2, odd heights.  Then the tile engine's four-channel loads.
+LARGE_SHAPES = [(61, 32, 34, 32, 40, 1), (31, 31, 35, 72, 72, 1), (31, 31, 35, 136, 40, 1), (31, 31, 35, 33, 136, 1),
+                (34, 31, 62, 97, 24, 2), (34, 31, 62, 97, 56, 2), (45, 31, 62, 72, 96, 2),
+                (3, 5, 22, 4, 44, 1), (2, 9, 30, 12, 20, 2), (4, 7, 26, 20, 68, 1), (3, 6, 18, 4, 8, 2)]
+
+
+@pytest.mark.parametrize("shape", LARGE_SHAPES, ids=[f"n{s[0]}_{s[1]}x{s[2]}_{s[3]}to{s[4]}_s{s[5]}" for s in LARGE_SHAPES])
+def test_conv_large_launches(gpu_lib, shape):
+    test_conv_gather_tile_edges(gpu_lib, shape)
 
 
 def test_conv_empty_batch(gpu_lib):
