@@ -54,6 +54,11 @@ __device__ __forceinline__ u32x4 load_b128(Rsrc r, uint32_t offset, uint32_t uni
     return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, offset, uniform, 0));
 }
 
+// Between LDS accesses by which a wavefront's lanes hand values to each other,
+// and before a buffer so read is written again: the hardware takes a
+// wavefront's accesses in order, the compiler knows only each lane's own.
+__device__ __forceinline__ void lds_handover() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local"); }
+
 // The weights of output channels n0 .. n0 + 16 NF - 1 for chunks c0 .. c0 +
 // count - 1 of the flattened (tap, chunk) list, as fragments of 1 KB: a
 // wavefront fetches every WAVES-th fragment, kBatch of them before it stores the
@@ -122,6 +127,7 @@ __device__ __forceinline__ void store_relu(const f32x4 *sums, const float *bias,
     constexpr int kPitch = 16 * NF, kUnits = 2 * NF;  // elements of a pixel, 8-channel units
     // pixels whose units share banks keep them in different order (32 -> 64 channels at batch 256: 13.8 us, 15.3 without)
     auto at = [](int px, int unit) { return px * kPitch + 8 * (unit ^ (px / (8 / NF) & (kUnits - 1))); };
+    lds_handover();
 #pragma unroll
     for (int f = 0; f < NF; f++) {
         const int k = 16 * f + 4 * (lane >> 4);
@@ -130,6 +136,7 @@ __device__ __forceinline__ void store_relu(const f32x4 *sums, const float *bias,
             bf16x4_of(make_float4(fmaxf(sums[f][0] + b.x, 0.f), fmaxf(sums[f][1] + b.y, 0.f),
                                   fmaxf(sums[f][2] + b.z, 0.f), fmaxf(sums[f][3] + b.w, 0.f)));
     }
+    lds_handover();
 #pragma unroll
     for (int i = 0; i < kUnits / 4; i++) {
         const int u = 64 * i + lane, m = m0 + u / kUnits, n = n0 + 8 * (u % kUnits);
@@ -204,9 +211,10 @@ __global__ __launch_bounds__(64 * WAVES, 4) void k_conv_gather(GatherArgs a) {
     auto use = [&](int d, int q) {
         bf16x8 fw[NF], fs[MT];
 #pragma unroll
-        for (int t = 0; t < MT; t++) fs[t] = chunk_fragment(buf + ((d & 1) * MT + t) * 64, lane);
-#pragma unroll
         for (int f = 0; f < NF; f++) fw[f] = __builtin_bit_cast(bf16x8, wf[(q * NF + f) * 64 + lane]);
+        lds_handover();
+#pragma unroll
+        for (int t = 0; t < MT; t++) fs[t] = chunk_fragment(buf + ((d & 1) * MT + t) * 64, lane);
         put((d + 1) % DEPTH);
         issue((d + 1) % DEPTH);
         // gradient: pixels as the result's rows, a lane's neighbours hold the next channels (64 bytes of FP32);
@@ -319,6 +327,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_conv_bwd_data_s2(GatherArgs a) {
     for (int s = 0; s < 4 * CHUNKS; s++) {
         const int shift = s / CHUNKS, chunk = s % CHUNKS, oy = shift < 2, ox = shift % 2 == 0;
         bf16x8 fs[MT];
+        lds_handover();
 #pragma unroll
         for (int t = 0; t < MT; t++) fs[t] = chunk_fragment(buf + ((s & 1) * MT + t) * 64, lane);
         if (s + 1 < 4 * CHUNKS) put(s + 1);
@@ -462,9 +471,11 @@ __global__ __launch_bounds__(256) void k_conv_fwd_rows(ConvShape c, const uint16
     const uint32_t *t0 = r + (2 * q) / 3 * kPitch + (2 * q) % 3 + 2 * i + 3,
                    *t1 = r + (2 * q + 1) / 3 * kPitch + (2 * q + 1) % 3 + 2 * i + 3, *t8 = r + 2 * kPitch + 2 + 2 * i + 3;
     for (; seg < segments; seg += 4 * gridDim.x) {
+        lds_handover();
 #pragma unroll
         for (int t = 0; t < 3; t++) *(u32x4 *)(r + t * kPitch + 4 + 4 * lane) = v[t];
         if (lane < 3) r[lane * kPitch + 3] = left;
+        lds_handover();
         if (seg + 4 * (int)gridDim.x < segments) fetch(seg + 4 * gridDim.x);
 #pragma unroll
         for (int g = 0; g < kSegment / 16; g++) {
