@@ -37,8 +37,9 @@ struct ups_batch {
     int *d_tile_start = nullptr;  // [4][n+1]
     unsigned *d_tile_of = nullptr;  // per level, (registration << 16) | tile of each tile (StepArgs::tile_of)
     int64_t tile_of_off[4] = {0, 0, 0, 0};
-    // the main loop's blocks: group[l] tiles of a registration each (0: one)
-    int group[4] = {0, 0, 0, 0}, total_blocks[4] = {0, 0, 0, 0};
+    // the main loop's blocks: group[l] tiles of a registration each, with or without a look at its flags first
+    int group[4] = {1, 1, 1, 1}, total_blocks[4] = {0, 0, 0, 0};
+    bool leave[4] = {false, false, false, false};
     unsigned *d_block_of = nullptr;  // per level, (registration << 16) | first tile of each block
     int64_t block_of_off[4] = {0, 0, 0, 0};
     int *d_pre_start = nullptr;   // [n+1]
@@ -134,22 +135,34 @@ int default_k(ups_context *ctx, int64_t npix) {
     return tuned > 0 ? tuned : 8;
 }
 
-// Tiles that a block of the main loop takes after one prologue (the reduction
-// of its registration's partials, the solve and the update); 0: one, in the
-// form of the kernel that does not look at its registration's flags first
-// (their round trip costs 0.3 us a launch), for launches whose blocks all run
-// at once.  Where six rounds of blocks remain, more tiles a block save
-// prologues and, once most registrations are done, blocks that only leave.
-// 256 uneven registrations, 15488 tiles of level 0, every one active / most of
-// them done: 222 / 38 us with one tile a block, 212 / 33 with two, 222 / 42
-// with four (and 62 us when a done registration's blocks still read its
-// partials).
-int tiles_per_block(int tiles) {
-    constexpr int kResidentBlocks = 1024;  // four on each of 256 CUs
-    if (tiles <= kResidentBlocks) return 0;
-    int g = 1;
-    while (g < 8 && tiles / (2 * g) >= 6 * kResidentBlocks) g *= 2;
-    return g;
+// How the blocks of the main loop's launch over `tiles` tiles are laid out
+// (FORM_TILE, FORM_LEAVE or FORM_TILES).  1024 blocks run at once, four on each
+// of 256 CUs.  us a register call of 10 iterations a level, FORM_TILE /
+// FORM_LEAVE / two tiles a block / four:
+//   tiles of level 0    with a stop criterion      without one
+//    2176                535/ 523/ 574              654/ 656/ 699
+//    7072               1213/1167/1211             1691/1685/1687
+//   13376               2037/1933/1943/2125        3028/3020/2973/3095
+//   29632               2806/2531/2438/2434        3919/3969/3816/3743
+//   51200               3291/2988/2318/2076        4354/4415/3437/3003
+// (uneven sizes, the last two with 4 and 1 pixels per thread).
+//
+// A block whose registration is done leaves on the flags instead of reading
+// its partials first; their round trip costs the others 0.3 us a launch, so
+// they are looked at where registrations stop and a third round of blocks
+// runs (the robust objective, which stops later: a fourth; 571/575 us at 2176
+// tiles, 724/722 at 3248).
+bool blocks_may_leave(int tiles, const ups_icp_params &p) {
+    return p.stop_update_norm > 0.0 && tiles > (p.irls_delta > 0.f ? 3 : 2) * 1024;
+}
+
+// Several tiles a block save prologues (reduction, solve) and blocks that only
+// leave, and make the last round longer.  Eight a block: 2135 and 2937 us at
+// 51200 tiles.  With FP32 sums the prologue is shorter: 1929/1835/1867 us at
+// 13376 tiles, 2682/2410/2337/2301 at 29632.
+int tiles_per_block(int tiles, const ups_icp_params &p) {
+    if (tiles >= 24 * 1024) return 4;
+    return tiles >= 12 * 1024 && p.precision != UPS_PREC_F32 ? 2 : 1;
 }
 
 // The pyramids a register / grid-search call builds: every image's, or in
@@ -341,10 +354,11 @@ ups_status ups_batch_create(ups_context *ctx, int32_t n, const ups_batch_item *i
     alloc((void **)&b->d_tile_of, std::max<size_t>(tile_of.size(), 1) * sizeof(unsigned));
     std::vector<unsigned> block_of;
     for (int l = 0; l < 4; l++) {
-        b->group[l] = tiles_per_block(b->total_tiles[l]);
+        b->group[l] = tiles_per_block(b->total_tiles[l], *p);
+        b->leave[l] = blocks_may_leave(b->total_tiles[l], *p);
         b->block_of_off[l] = (int64_t)block_of.size();
         for (int k = 0; k < n; k++)
-            for (int t = 0; t < (l < L ? hi[k].nblocks[l] : 0); t += std::max(b->group[l], 1))
+            for (int t = 0; t < (l < L ? hi[k].nblocks[l] : 0); t += b->group[l])
                 block_of.push_back(((unsigned)k << 16) | (unsigned)t);
         b->total_blocks[l] = (int)((int64_t)block_of.size() - b->block_of_off[l]);
     }
@@ -506,7 +520,8 @@ ups_status ups_batch_time_iteration(ups_context *ctx, ups_batch *b, int32_t leve
     a.irls_delta = b->p.irls_delta;
     a.min_inliers = b->p.min_inliers;
     a.tile_of = b->d_block_of + b->block_of_off[level];
-    a.group = b->group[level];
+    a.group = (int16_t)b->group[level];
+    a.leave = b->leave[level];
     ups_status st;
     if ((st = launch_activate_batch(b->d_inst, b->n, s)) != UPS_OK) return st;
     hipEvent_t e0, e1;
@@ -609,7 +624,8 @@ ups_status register_batch_fused(ups_batch *b, const ups_pose *init_d, ups_icp_re
         a.level = l;
         a.d_max2 = p.d_max[l] * p.d_max[l];
         a.tile_of = b->d_block_of + b->block_of_off[l];
-        a.group = b->group[l];
+        a.group = (int16_t)b->group[l];
+        a.leave = b->leave[l];
         for (int it = 0; it < p.iters[l]; it++) {
             a.parity = parity;
             a.first_of_level = it == 0;
@@ -627,7 +643,7 @@ ups_status register_batch_fused(ups_batch *b, const ups_pose *init_d, ups_icp_re
     a.tau2 = a.d_max2;
     a.check_max_iters = (p.stop_update_norm > 0.0 && p.iters[0] > 0);
     a.tile_of = b->d_block_of + b->block_of_off[0];
-    a.group = b->group[0];
+    a.group = (int16_t)b->group[0];
     if ((st = launch_icp_batch(b->K[0], p.precision, MODE_EVAL, b->d_inst, b->d_tile_start, n, a, b->total_blocks[0],
                                s, true)) != UPS_OK)
         return st;

@@ -1,6 +1,8 @@
 // Registration descriptors shared by the single and batched ICP launchers.
 #pragma once
 
+#include <cstddef>
+
 #include "ups_internal.hpp"
 
 namespace ups {
@@ -8,6 +10,11 @@ namespace ups {
 // MODE_SCHED: an iteration tile of the persistent batch kernel (the
 // iteration sums; state and partial exchanged as agent-coherent words).
 enum { MODE_ITER = 0, MODE_EVAL = 1, MODE_SCHED = 2 };
+
+// A block of the batch's fused launches: one tile; one tile, but a block whose
+// registration has nothing left to do leaves on the state's flags, before it
+// reads any partial; or several tiles after one prologue, with the flags.
+enum { FORM_TILE = 0, FORM_LEAVE = 1, FORM_TILES = 2 };
 
 // Registration state, two ping-pong slots per registration.
 struct RegState {
@@ -23,6 +30,10 @@ struct RegState {
     int active;         // batches: the next Gauss-Newton launch processes this registration
     int skip;           // batches: the registration takes no part in this call (masked out)
 };
+// read together by a block that may leave
+static_assert(offsetof(RegState, level_active) == offsetof(RegState, stop) + 4 &&
+                  offsetof(RegState, pending) == offsetof(RegState, stop) + 8,
+              "stop, level_active and pending lie side by side");
 
 // One registration as the kernels see it.  Batches read pyramid images of
 // each level (scan[l], kf[l]); single registrations (the fused kernels) read
@@ -68,10 +79,10 @@ struct StepArgs {
     int min_inliers;
     double stop_norm;
     int kpt;  // MODE_SCHED: pixels per thread of this tile (<= the kernel's K, a multiple of its pixel groups)
-    // batches, fused launches: 0: a block per tile; else blocks of `group`
-    // tiles (tile_of lists each block's first), which leave early where their
-    // registration is done
-    int group;
+    // batches, fused launches: FORM_TILES with `group` tiles a block (tile_of
+    // lists each block's first) where that is more than one, else FORM_LEAVE
+    // with `leave`, else FORM_TILE
+    int16_t group, leave;
     const ups_pose *init;  // single registrations: the first launch builds the state from this start pose
     int reverse_tiles;  // debug: workgroups take the tiles in reverse order (set by the launchers)
     int seq;            // single registrations: the launch's number within the call (phase timestamps)

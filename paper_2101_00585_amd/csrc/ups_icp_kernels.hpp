@@ -708,16 +708,15 @@ struct IcpShared {
     int job[8];  // persistent scheduler: ticket's registration and tile, last-arriver flag, spare, job (4 words)
 };
 
-// MULTI: the block takes the tiles tile .. tile_end-1 after one prologue, each
-// with sums and a partial of its own (the same partials as a block per tile
-// leaves), and a block whose registration has nothing left to do leaves on the
-// state's flags, before it reads any partial.
+// FORM_TILES: the block takes the tiles tile .. tile_end-1 after one prologue,
+// each with sums and a partial of its own (the same partials as a block per
+// tile leaves).
 template <int K, int PREC, int MODE, bool FUSED, bool WORLD, bool IRLS, bool STRIDED = FUSED, bool COH = false,
-          bool MULTI = false>
+          int FORM = FORM_TILE>
 __device__ __forceinline__ void icp_tile(const Inst &I, const StepArgs &a, const int tile,
                                          IcpShared<AccOf<PREC>> &sh, const int tile_end = 0) {
     static_assert(!COH || (FUSED && MODE == MODE_ITER), "coherent hand-over: fused iterations only");
-    static_assert(!MULTI || (FUSED && !STRIDED && !COH), "several tiles a block: the batch's main loop");
+    static_assert(FORM == FORM_TILE || (FUSED && !STRIDED && !COH), "flags, several tiles: the batch's main loop");
     constexpr int NV = (MODE == MODE_EVAL) ? 31 : 29;  // EVAL adds valid count and truncated cost
     using Acc = AccOf<PREC>;
     const int tid = threadIdx.x;
@@ -727,7 +726,7 @@ __device__ __forceinline__ void icp_tile(const Inst &I, const StepArgs &a, const
     const double *part_in = I.partials + (size_t)a.parity * I.pstride * kPartialStride;
     double *part_out = I.partials + (size_t)(FUSED ? (a.parity ^ 1) : 0) * I.pstride * kPartialStride;
 
-    if constexpr (MULTI && MODE == MODE_ITER) {
+    if constexpr (FORM != FORM_TILE && MODE == MODE_ITER) {
         // scalar loads (the descriptor is block-uniform, the state the previous launch's)
         const int UPS_AS_CONST *f = (const int UPS_AS_CONST *)&slot_in->stop;
         const int stop = f[0], level_active = f[1], pending = f[2];
@@ -912,7 +911,7 @@ __device__ __forceinline__ void icp_tile(const Inst &I, const StepArgs &a, const
     }
 
     UPS_PHASE(kPh, tile, a.seq, 3);
-    if constexpr (MULTI) {
+    if constexpr (FORM == FORM_TILES) {
         // the next tile's first scan surfels are in flight behind this tile's reduction
         base += kBlock * KL;
         pw0 = __builtin_amdgcn_readfirstlane(base + (tid & ~63));
@@ -936,7 +935,7 @@ __device__ __forceinline__ void icp_tile(const Inst &I, const StepArgs &a, const
         else
             block_partial<NV, Acc, MODE == MODE_SCHED>(x, qbuf, part_out, I.pstride, tl, tot);
     }
-    if constexpr (!MULTI) break;
+    if constexpr (FORM != FORM_TILES) break;
     else {
         if (++tl >= tile_end) break;
         __syncthreads();  // the reduction's buffer is free again
@@ -957,10 +956,10 @@ __device__ __forceinline__ void icp_tile(const Inst &I, const StepArgs &a, const
     UPS_PHASE_LAST(kPh, a.seq);
 }
 
-template <int K, int PREC, int MODE, bool FUSED, bool WORLD, bool IRLS, bool STRIDED = FUSED, bool MULTI = false>
+template <int K, int PREC, int MODE, bool FUSED, bool WORLD, bool IRLS, bool STRIDED = FUSED, int FORM = FORM_TILE>
 __device__ __forceinline__ void icp_block(const Inst &I, const StepArgs &a, int tile, int tile_end = 0) {
     __shared__ IcpShared<AccOf<PREC>> sh;
-    icp_tile<K, PREC, MODE, FUSED, WORLD, IRLS, STRIDED, false, MULTI>(I, a, tile, sh, tile_end);
+    icp_tile<K, PREC, MODE, FUSED, WORLD, IRLS, STRIDED, false, FORM>(I, a, tile, sh, tile_end);
 }
 
 // Workgroups are dealt to the 8 XCDs in turn (workgroup i to XCD i mod 8), and
@@ -1089,19 +1088,19 @@ __global__ __launch_bounds__(kBlock) void k_icp_level_xcd(Inst I, StepArgs a, in
 // load), or by binary search in the level's prefix table of tile counts
 // (tile_start[n] = total blocks; a chain of dependent loads at the head of
 // every block).  FUSED: each block first applies its registration's pending
-// update (the batch's main loop; MULTI: and then takes a.group tiles, of which
-// the table names the first); otherwise slot 0 holds the pose (the
+// update (the batch's main loop; FORM_TILES: and then takes a.group tiles, of
+// which the table names the first); otherwise slot 0 holds the pose (the
 // subset and scheduled paths, timing).
-template <int K, int PREC, int MODE, bool IRLS, bool FUSED, bool MULTI = false>
+template <int K, int PREC, int MODE, bool IRLS, bool FUSED, int FORM = FORM_TILE>
 __global__ __launch_bounds__(kBlock) void k_icp_batch(const Inst *__restrict__ insts,
                                                       const int *__restrict__ tile_start, int n, StepArgs a) {
     const int b = xcd_tile(blockIdx.x, gridDim.x, a.reverse_tiles);
-    if (a.tile_of) {
+    if (FORM == FORM_TILES || a.tile_of) {
         const unsigned v = a.tile_of[b];
         const Inst &I = insts[v >> 16];
         const int tile = (int)(v & 0xFFFFu);
-        icp_block<K, PREC, MODE, FUSED, false, IRLS, false, MULTI>(I, a, tile,
-                                                                   min(tile + a.group, I.nblocks[a.level]));
+        icp_block<K, PREC, MODE, FUSED, false, IRLS, false, FORM>(I, a, tile,
+                                                                  min(tile + a.group, I.nblocks[a.level]));
         return;
     }
     int lo = 0, hi = n;  // the last k with tile_start[k] <= b
@@ -1110,8 +1109,21 @@ __global__ __launch_bounds__(kBlock) void k_icp_batch(const Inst *__restrict__ i
         if (tile_start[mid] <= b) lo = mid;
         else hi = mid;
     }
-    icp_block<K, PREC, MODE, FUSED, false, IRLS, false, MULTI>(insts[lo], a, b - tile_start[lo],
-                                                               b - tile_start[lo] + 1);
+    icp_block<K, PREC, MODE, FUSED, false, IRLS, false, FORM>(insts[lo], a, b - tile_start[lo]);
+}
+
+// The batch's fused launches, in the form that the arguments ask for.
+template <int K, int PREC, bool IRLS>
+inline void launch_fused(int mode, const Inst *insts, const int *tile_start, int n, const StepArgs &a0, int blocks,
+                         hipStream_t s) {
+    const StepArgs a = with_tile_order(a0);
+    auto go = [&](auto kernel) { kernel<<<dim3(blocks), dim3(kBlock), 0, s>>>(insts, tile_start, n, a); };
+    if (mode != MODE_ITER) {
+        if (a.group > 1) go(k_icp_batch<K, PREC, MODE_EVAL, IRLS, true, FORM_TILES>);
+        else go(k_icp_batch<K, PREC, MODE_EVAL, IRLS, true>);
+    } else if (a.group > 1) go(k_icp_batch<K, PREC, MODE_ITER, IRLS, true, FORM_TILES>);
+    else if (a.leave) go(k_icp_batch<K, PREC, MODE_ITER, IRLS, true, FORM_LEAVE>);
+    else go(k_icp_batch<K, PREC, MODE_ITER, IRLS, true>);
 }
 
 // A subset of the batch (a Compact list), in the main loop's fused form: a

@@ -419,3 +419,40 @@ def test_blocks_of_several_tiles_give_the_same_bytes(gpu_lib, precision, irls):
         for k in range(n):
             assert np.array_equal(got[k], small[k % 6]), (n, k)
     ctx.close()
+
+
+@pytest.mark.parametrize("stop", [0.0, 1e-4])
+@pytest.mark.parametrize("precision,irls", [(0, 0.0), (0, 0.01), (1, 0.0), (2, 0.0)])
+def test_block_forms_give_the_same_bytes(gpu_lib, precision, irls, stop):
+    """The main loop's blocks: where a third round of them runs (a fourth with the
+    robust objective) those of a batch with a stop criterion leave on their
+    registration's flags, and from 24,576 tiles on a block takes four tiles
+    (27, 29, 30 and 128 a registration: last blocks of three, one, two and four).
+    Batches of 3,424 and of 25,094 tiles of level 0 give the bytes of one of 428,
+    whose blocks take one tile and read their partials first."""
+    import torch
+    sizes = [(54, 128), (58, 128), (60, 128), (64, 512)]
+    pairs = [W.batch_pair(k, base_seed=7200, max_angle=np.radians(6), max_trans=0.4, size=sizes[k % 4]) for k in range(8)]
+    n_max = 470
+    ctx = gpu_lib.Context(0, max_pixels=1 << 16, max_batch=n_max, max_batch_pixels=n_max * 64 * 512)
+    base = []
+    for p in pairs:
+        g = p["geom"]
+        s, k = (gpu_lib.panorama_normals(ctx, g, torch.from_numpy(p[c]).cuda()) for c in ("scan", "kf"))
+        base.append(dict(scan_geom=g, kf_geom=g, scan_surfel=s, kf_surfel=k))
+    prm = gpu_lib.IcpParams(levels=2, iters=(7, 5, 0, 0), stop_update_norm=stop, precision=precision, irls_delta=irls)
+    init = torch.stack([gpu_lib.pose_tensor(np.eye(4))] * n_max)
+
+    def run(items):
+        b = gpu_lib.Batch(ctx, items, prm, pixels_per_thread=1)
+        out = b.register(init[:len(items)].contiguous()).cpu().numpy()
+        b.close()
+        return out
+
+    small = run(base)
+    assert {r["status"] for r in gpu_lib.read_results(torch.from_numpy(small))} <= {0, 1}
+    for n in (64, n_max):
+        got = run([base[k % 8] for k in range(n)])
+        for k in range(n):
+            assert np.array_equal(got[k], small[k % 8]), (n, k)
+    ctx.close()
