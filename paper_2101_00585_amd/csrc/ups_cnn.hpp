@@ -48,6 +48,12 @@ __device__ __forceinline__ float4 load_f4(const float *p) {
 }
 __device__ __forceinline__ void store_f4(float *p, f32x4 v) { *(PackedF4 *)p = PackedF4{v[0], v[1], v[2], v[3]}; }
 
+// A buffer descriptor: loads through it at or past `bytes` read 0.
+typedef __amdgpu_buffer_rsrc_t Rsrc;
+__device__ __forceinline__ Rsrc rsrc_of(const void *p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00027000);
+}
+
 // A 3x3 convolution on NHWC tensors: width circular, height zero-padded,
 // output (h-1)/stride+1 x (w-1)/stride+1.
 struct ConvShape {

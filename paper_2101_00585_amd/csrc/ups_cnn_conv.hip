@@ -46,10 +46,6 @@ struct GatherArgs {
 constexpr uint32_t kMaxBytes = 0x80000000u;
 template <bool GRAD>
 constexpr uint32_t kNone = kMaxBytes / (GRAD ? 4 : 2);
-typedef __amdgpu_buffer_rsrc_t Rsrc;
-__device__ __forceinline__ Rsrc rsrc_of(const void *p, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00027000);
-}
 __device__ __forceinline__ u32x4 load_b128(Rsrc r, uint32_t offset, uint32_t uniform = 0) {
     return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, offset, uniform, 0));
 }

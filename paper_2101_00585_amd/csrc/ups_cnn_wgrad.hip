@@ -51,7 +51,12 @@ constexpr int kRowTile = 288, kPix = 64, kWideThreads = 576;
 // 256: 25.7, 26.6, 16.7 and 18.7 us with the reduction, against 177.5, 165.6,
 // 68.6 and 78 on 64 x 64 tiles gathered along pixels by 2-byte loads.  UNIT:
 // elements per load of x (8 where cin is a multiple of 8, 2 where it is even,
-// else 1).
+// else 1, whose 32 loads a step leave registers for one step in flight).
+// Window elements shorter than a vector load come through a buffer descriptor,
+// no load behind a branch: a load whose result joins another's in one
+// register inside a branch waits there (65536 pixels of 5, 33 and 4 -> 64
+// channels: 22.8, 59.8 and 18.4 us so; 53.7, 119.8 and 30.7 with branches and a
+// division an element).
 template <int NF, int UNIT>
 __global__ __launch_bounds__(kWideThreads) void k_conv_wgrad(WgradArgs a) {
     constexpr int kXP = kRowTile * 2 + 32;                      // 19 x 32 bytes
@@ -67,35 +72,42 @@ __global__ __launch_bounds__(kWideThreads) void k_conv_wgrad(WgradArgs a) {
     const int r8 = t % 36, pr = 4 * (t / 36), r = row0 + 8 * r8;
     const int tap = r / c.cin, ci = r - tap * c.cin;
     const Tap at(c, tap / 3, tap % 3);
+    // the same for single elements: window row ky0, element k0 of its 3 cin in memory order
+    const int row_k = 3 * c.cin, ky0 = r / row_k, k0 = r - ky0 * row_k;
+    const Tap at0(c, ky0, 0), at1(c, ky0 + 1, 0);
+    const int last_ox = c.stride * (c.wo - 1) + 1 == c.w ? c.wo - 1 : -1;
+    const Rsrc xr = rsrc_of(a.x, 2 * (uint32_t)(c.n * c.h * c.w) * (uint32_t)c.cin);
+    constexpr uint32_t kNowhere = UNIT == 2 ? 0xFFFFFFFCu : 0xFFFFFFFEu;  // past every tensor
     PixelWalk px;
     px.start(c, p_begin + pr);
     const int gp = t / (2 * NF), gc = co0 + 8 * (t % (2 * NF));
+    constexpr int kStages = UNIT == 1 ? 1 : 2;
     struct Staged {
-        uint4 x[4];
+        uint32_t x[4][8 / UNIT * (UNIT == 8 ? 4 : 1)];
         float4 dy[2];
         uint2 y[2];
-    } st[2];
+    } st[kStages];
     auto fetch = [&](Staged &f, int p0) {
         PixelWalk w = px;
 #pragma unroll
         for (int i = 0; i < 4; i++) {
             const int p = p0 + pr + i;
-            f.x[i] = make_uint4(0, 0, 0, 0);
             if constexpr (UNIT == 8) {
-                if (p < p_end && r < rows && at.inside(w)) f.x[i] = load_u4(a.x + at.at(w) + ci);
+                uint4 v = make_uint4(0, 0, 0, 0);
+                if (p < p_end && r < rows && at.inside(w)) v = load_u4(a.x + at.at(w) + ci);
+                f.x[i][0] = v.x, f.x[i][1] = v.y, f.x[i][2] = v.z, f.x[i][3] = v.w;
             } else {
-                uint32_t v[4] = {0, 0, 0, 0};
-                if (p < p_end)
+                const bool on0 = p < p_end && ky0 < 3 && at0.inside(w), on1 = p < p_end && ky0 < 2 && at1.inside(w);
+                const int left = w.ox == 0 ? c.w * c.cin : 0, right = w.ox == last_ox ? c.w * c.cin : 0;
 #pragma unroll
-                    for (int e = 0; e < 8; e += UNIT) {
-                        const int re = r + e, te = re / c.cin, ce = re - te * c.cin;
-                        const Tap ate(c, te / 3, te % 3);
-                        if (re < rows && ate.inside(w)) {
-                            if constexpr (UNIT == 2) v[e >> 1] = *(const uint32_t *)(a.x + ate.at(w) + ce);
-                            else v[e >> 1] |= (uint32_t)a.x[ate.at(w) + ce] << (16 * (e & 1));
-                        }
-                    }
-                f.x[i] = make_uint4(v[0], v[1], v[2], v[3]);
+                for (int e = 0; e < 8; e += UNIT) {
+                    const bool next = k0 + e >= row_k;  // of the next window row
+                    const int k = k0 + e - (next ? row_k : 0);
+                    const uint32_t o = w.centre + (next ? at1.off : at0.off) + k + (k < c.cin ? left : k >= 2 * c.cin ? -right : 0);
+                    const uint32_t b = (next ? on1 : on0) ? 2 * o : kNowhere;
+                    f.x[i][e / UNIT] = UNIT == 2 ? (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(xr, b, 0, 0)
+                                                 : (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(xr, b, 0, 0);
+                }
             }
             if (i < 3) w.next(a.walk);
         }
@@ -124,14 +136,19 @@ __global__ __launch_bounds__(kWideThreads) void k_conv_wgrad(WgradArgs a) {
     auto step = [&](Staged &f, int buf, int p0) {
         uint8_t *x = xs[buf], *g = gs[buf];
 #pragma unroll
-        for (int i = 0; i < 4; i++) *(uint4 *)(x + (pr + i) * kXP + 16 * r8) = f.x[i];
+        for (int i = 0; i < 4; i++) {
+            const uint32_t *v = f.x[i];
+            *(uint4 *)(x + (pr + i) * kXP + 16 * r8) =
+                UNIT == 1 ? make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16)
+                          : make_uint4(v[0], v[1], v[2], v[3]);
+        }
         if (gp < kPix) {
             const uint2 lo = masked_grad4(f.y[0], f.dy[0]), hi = masked_grad4(f.y[1], f.dy[1]);
             *(uint4 *)(g + gp * kGP + 16 * (t % (2 * NF))) = make_uint4(lo.x, lo.y, hi.x, hi.y);
         }
         // the buffer's readers of two steps ago passed the last step's barrier
         __syncthreads();
-        if (p0 + 2 * kPix < p_end) fetch(f, p0 + 2 * kPix);
+        if (p0 + kStages * kPix < p_end) fetch(f, p0 + kStages * kPix);
 #pragma unroll
         for (int kc = 0; kc < kPix; kc += 32) {
             bf16x8 fx[2], fg[NF];
@@ -150,10 +167,10 @@ __global__ __launch_bounds__(kWideThreads) void k_conv_wgrad(WgradArgs a) {
         }
     };
     if (p_begin < p_end) fetch(st[0], p_begin);
-    if (p_begin + kPix < p_end) fetch(st[1], p_begin + kPix);
+    if (kStages > 1 && p_begin + kPix < p_end) fetch(st[kStages - 1], p_begin + kPix);
     for (int p0 = p_begin; p0 < p_end; p0 += 2 * kPix) {
         step(st[0], 0, p0);
-        if (p0 + kPix < p_end) step(st[1], 1, p0 + kPix);
+        if (p0 + kPix < p_end) step(st[kStages - 1], 1, p0 + kPix);
     }
     float *part = a.part + (size_t)blockIdx.z * (rows + 1) * c.cout;
 #pragma unroll

@@ -104,6 +104,17 @@ def test_conv_weight_gradient_tile_edges(gpu_lib, shape):
     assert (np.abs(_np(db) - db_ref) <= bound * db_abs).all(), np.abs(_np(db) - db_ref).max()
 
 
+# loads of one and two elements: eight rows that end one window row and start the next, both side columns on one output,
+# windows without an upper and a lower row, several steps, the largest of their channel tiles
+SHORT_LOADS = [(2, 3, 2, 4, 8, 2), (1, 1, 5, 7, 4, 1), (3, 5, 6, 5, 36, 2), (5, 6, 9, 4, 36, 1), (70, 4, 6, 9, 8, 1),
+               (2, 7, 3, 6, 132, 1), (4, 9, 20, 63, 40, 2), (1, 2, 2, 11, 4, 2)]
+
+
+@pytest.mark.parametrize("shape", SHORT_LOADS, ids=[f"n{s[0]}_{s[1]}x{s[2]}_{s[3]}to{s[4]}_s{s[5]}" for s in SHORT_LOADS])
+def test_conv_weight_gradient_short_loads(gpu_lib, shape):
+    test_conv_weight_gradient_tile_edges(gpu_lib, shape)
+
+
 @pytest.mark.parametrize("n", [1, 15, 16, 17, 33, 65, 130])
 def test_conv_weight_gradient_split_counts(gpu_lib, n):
     """n splits of 64 pixels each, around the sixteen sums and the two splits in
