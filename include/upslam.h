@@ -426,7 +426,11 @@ ups_status ups_batch_fallback_run(ups_context *ctx, ups_batch *b, ups_icp_result
  * h = (n_xy - 1) / 2.  scores_d: caller-owned int32 [n][C] workspace, C =
  * n_yaw n_xy^2 <= 65535, left holding every candidate's score.  Builds the
  * batch's pyramids from the level-0 surfel images first; enqueues only
- * kernels.  The best poses can start ups_register_batch. */
+ * kernels.  The best poses can start ups_register_batch.  Scratch: tables of
+ * the keyframes' points, about 8 bytes per keyframe pixel at level 0, in the
+ * batch's scratch for normals where its items have depth images, else laid out
+ * by ups_batch_create if the memory is there (without them the search reads
+ * the keyframes' images, the same scores, slower). */
 typedef struct {
     int32_t level;
     int32_t n_yaw, n_xy;

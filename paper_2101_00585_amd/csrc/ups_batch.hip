@@ -44,7 +44,10 @@ struct ups_batch {
     int64_t block_of_off[4] = {0, 0, 0, 0};
     int *d_pre_start = nullptr;   // [n+1]
     float4 *pyr = nullptr;
-    char *grid_points = nullptr;  // the grid search's keyframe tables of the levels 1 and up
+    // the grid search's keyframe tables of the levels 1 and up: in the normals' temporary images, which no search
+    // needs, where these are large enough, else in memory of their own, or null where there is none left (the search
+    // then reads the keyframes' images)
+    char *grid_points = nullptr, *grid_own = nullptr;
     int64_t *d_points_off = nullptr;  // [4][n] byte offsets of the tables in it
     bool points_level[4] = {false, false, false, false};  // levels that have them
     RegState *state = nullptr;    // [n][2]
@@ -105,7 +108,7 @@ void free_batch(ups_batch *b) {
     (void)hipFree(b->d_block_of);
     (void)hipFree(b->d_pre_start);
     (void)hipFree(b->pyr);
-    (void)hipFree(b->grid_points);
+    (void)hipFree(b->grid_own);
     (void)hipFree(b->d_points_off);
     (void)hipFree(b->state);
     (void)hipFree(b->partials);
@@ -376,7 +379,6 @@ ups_status ups_batch_create(ups_context *ctx, int32_t n, const ups_batch_item *i
             points_total += (int64_t)(grid_points_bytes(hi[k].kg[l]) + 15) / 16 * 16;
         }
     }
-    alloc((void **)&b->grid_points, (size_t)points_total);
     alloc((void **)&b->d_points_off, points_off.size() * sizeof(int64_t));
     alloc((void **)&b->state, (size_t)n * 2 * sizeof(RegState));
     pstride = (int)partial_stride(pstride);
@@ -451,6 +453,15 @@ ups_status ups_batch_create(ups_context *ctx, int32_t n, const ups_batch_item *i
         b->n_nimg = (int)nimg.size();
         b->total_ntiles = (int)ntile_of.size();
         alloc((void **)&b->d_ntile_of, ntile_of.size() * sizeof(unsigned));
+    }
+    if (points_total <= ntmp_total * (int64_t)sizeof(float4)) b->grid_points = (char *)b->ntmp;
+    else if (e == hipSuccess) {
+        // after everything a batch cannot do without
+        if (hipMalloc((void **)&b->grid_own, (size_t)points_total) != hipSuccess) {
+            b->grid_own = nullptr;
+            (void)hipGetLastError();
+        }
+        b->grid_points = b->grid_own;
     }
     if (e == hipSuccess) e = hipMemcpy(b->d_inst, hi.data(), n * sizeof(Inst), hipMemcpyHostToDevice);
     if (e == hipSuccess)

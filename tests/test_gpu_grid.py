@@ -253,3 +253,45 @@ def test_points_of_denormal_range_project_nowhere(gpu_lib):
         assert np.array_equal(score(1), full[:, 3:4, 3:4])
     b.close()
     ctx.close()
+
+
+def test_keyframe_tables_take_the_normals_scratch(gpu_lib):
+    """A batch whose items have depth images lays the grid search's tables out
+    in its scratch for normals: it takes the memory of the normals (16 bytes a
+    pixel) less the tables (24 bytes an entry) more than a batch of the same
+    surfel images alone, and a search between normals and registrations
+    changes neither."""
+    import torch
+    n, rows, cols, levels = 48, 128, 2048, 3
+    pair = W.batch_pair(0, base_seed=5_500_000, max_angle=math.radians(20.0), size=(rows, cols))
+    g = pair["geom"]
+    ctx = gpu_lib.Context(0, max_pixels=rows * cols, max_batch=n, max_batch_pixels=n * rows * cols)
+    full = _items([pair] * n)
+    bare = [{k: v for k, v in it.items() if "depth" not in k} for it in full]
+    params = gpu_lib.IcpParams(levels=levels, iters=(4, 4, 4))
+    taken = {}
+    gp = gpu_lib.GridParams(level=1, n_yaw=4, n_xy=2, xy_step=0.5, d_max=1.0)
+    found = {}
+    for name, items in (("warm", full), ("depth", full), ("bare", bare)):
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        b = gpu_lib.Batch(ctx, items, params)
+        torch.cuda.synchronize()
+        taken[name] = before - torch.cuda.mem_get_info()[0]
+        if name == "depth":
+            b.normals()
+            plain = b.register([np.eye(4)] * n).cpu().numpy()
+            b.grid_search(gp)
+            b.normals()
+            again = b.register([np.eye(4)] * n).cpu().numpy()
+            assert np.array_equal(plain, again)
+        found[name] = b.grid_search(gp)[2].cpu().numpy()
+        b.close()
+    ctx.close()
+    assert found["depth"].max() > 0 and np.array_equal(found["depth"], found["bare"])
+    normals = 2 * n * rows * cols * 16
+    tables = sum(n * ((rows >> l) * ((cols >> l) + 1) + 1) * 24 for l in range(1, levels))
+    print(f"[grid] {taken['depth'] / 2**20:.1f} MiB with depth images, {taken['bare'] / 2**20:.1f} without, "
+          f"normals {normals / 2**20:.1f}, tables {tables / 2**20:.1f}")
+    # the normals' lists of tiles, and the allocator's granularity of 2 MiB in a few allocations
+    assert taken["depth"] - taken["bare"] <= normals - tables + (16 << 20)
