@@ -507,11 +507,13 @@ void launch_s2(const GatherArgs &a, int M, hipStream_t s) {
 }  // namespace
 
 // Eight channels a load; byte offsets below kMaxBytes; with stride 2 a data
-// gradient's weights of 32 input channels in LDS.
+// gradient's weights of 32 input channels in LDS; with stride 1 more than eight
+// output channels, whose chunks of 32 would be three quarters empty (524288
+// pixels of 40 -> 8 channels: 89.9 us, 45.1 on 64 x 64 tiles).
 bool conv_gather_fits(const ConvShape &c, bool grad) {
     const int64_t ck = grad ? c.cout : c.cin, pixels = (int64_t)c.n * (grad ? c.ho * c.wo : c.h * c.w);
     return ck % 8 == 0 && pixels * ck * (grad ? 4 : 2) <= (int64_t)kMaxBytes &&
-           18 * (int64_t)c.cin * c.cout <= (int64_t)kMaxBytes && (!grad || c.stride == 1 || ck <= 128);
+           18 * (int64_t)c.cin * c.cout <= (int64_t)kMaxBytes && (!grad || (c.stride == 1 ? ck > 8 : ck <= 128));
 }
 
 bool conv_narrow_fits(const ConvShape &c) {
@@ -558,7 +560,14 @@ ups_status launch_conv_gather_bwd_data(const ConvShape &c, const uint16_t *y, co
     const int M = c.n * c.ho * c.wo;  // positions: pixels, or 2 x 2 pixels
     const bool many = M / 128 * ((a.N + 31) / 32) >= 512;
     if (c.stride == 1) {
-        if (many) launch_gather<true, 2, 2, 4, 2>(a, M, s);
+        // us for blocks of 64 pixels x 32 channels / 128 x 32 / 128 x 64 / 64 x 64 tiles:
+        //   32768 px, 128->128   71.0/101.8/ 56.6/ 82.9     16384 px, 64->64 (too few blocks)  10.2/12.2/10.7/23.3
+        //   524288 px, 40->16   107.7/ 92.1/ 62.1/ 67.6     524288 px, 16->16                  54.9/47.4/59.4/62.0
+        //                                                   524288 px, 2->128                 271.2/368.2/340.2/632.0
+        // 64 channels a block mask and round each gradient half as often; 128 pixels use each weight fragment twice, but
+        // with the weights of more than 64 channels LDS holds one block a CU
+        if (a.N > 32 && M / 128 * ((a.N + 63) / 64) >= 256) launch_gather<true, 4, 1, 8, 4>(a, M, s);
+        else if (many && a.chunks <= 2) launch_gather<true, 2, 2, 4, 2>(a, M, s);
         else launch_gather<true, 2, 1, 4, 4>(a, M, s);
     } else if (many && a.chunks <= 3) {
         if (a.chunks == 1) launch_s2<1, 2>(a, M, s);

@@ -157,9 +157,9 @@ def test_conv_gather_tile_edges(gpu_lib, shape):
 
 
 # launches of many pixels, whose blocks take larger tiles: k_conv_gather<forward, 4, 2, 8, 2> with its weights in one piece
-# and in several, <forward, 2, 2, 8, 4> in several, <gradient, 2, 2, 4, 2> in one piece and in several, and
-# k_conv_bwd_data_s2 for 1, 2 and 3 chunks of output channels; each past its threshold by a partial last block, with
-# channels past a tile's end and, at stride 2, odd heights.  Then the tile engine's four-channel loads.
+# and in several, <forward, 2, 2, 8, 4> in several, <gradient, 2, 2, 4, 2>, <gradient, 4, 1, 8, 4> in one piece and
+# in several, and k_conv_bwd_data_s2 for 1, 2 and 3 chunks of output channels; each past its threshold by a partial last
+# block, with channels past a tile's end and, at stride 2, odd heights.  Then the tile engine's four-channel loads.
 LARGE_SHAPES = [(61, 32, 34, 32, 40, 1), (31, 31, 35, 72, 72, 1), (31, 31, 35, 136, 40, 1), (31, 31, 35, 33, 136, 1),
                 (34, 31, 62, 97, 24, 2), (34, 31, 62, 97, 56, 2), (45, 31, 62, 72, 96, 2),
                 (3, 5, 22, 4, 44, 1), (2, 9, 30, 12, 20, 2), (4, 7, 26, 20, 68, 1), (3, 6, 18, 4, 8, 2)]
@@ -167,6 +167,15 @@ LARGE_SHAPES = [(61, 32, 34, 32, 40, 1), (31, 31, 35, 72, 72, 1), (31, 31, 35, 1
 
 @pytest.mark.parametrize("shape", LARGE_SHAPES, ids=[f"n{s[0]}_{s[1]}x{s[2]}_{s[3]}to{s[4]}_s{s[5]}" for s in LARGE_SHAPES])
 def test_conv_large_launches(gpu_lib, shape):
+    test_conv_gather_tile_edges(gpu_lib, shape)
+
+
+# data gradients of stride 1 over eight channels, which the tile engine takes, and over sixteen, 64 and 72: 128 pixels and
+# 64 channels a block, or 64 pixels and 32
+@pytest.mark.parametrize("shape", [(2, 5, 18, 36, 8, 1), (31, 31, 35, 40, 8, 1), (31, 31, 35, 40, 16, 1),
+                                   (31, 31, 35, 72, 64, 1), (61, 32, 34, 24, 72, 1)],
+                         ids=lambda s: f"n{s[0]}_{s[1]}x{s[2]}_{s[3]}to{s[4]}")
+def test_conv_data_gradient_few_channels(gpu_lib, shape):
     test_conv_gather_tile_edges(gpu_lib, shape)
 
 
