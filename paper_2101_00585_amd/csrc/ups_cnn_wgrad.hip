@@ -22,8 +22,9 @@ struct WgradArgs {
     WalkArgs walk;
     const uint16_t *x, *y;
     const float *dy;
-    float *part;  // [split][9 cin + 1][cout]
-    int chunk;    // output pixels of a split
+    float *w_sums, *b_sums;  // [9 cin][cout] and [cout] of the first split
+    int64_t split_stride;    // from a split's sums to the next one's
+    int chunk;               // output pixels of a split
 };
 
 // Fragment of rows e0 .. e0+15 over the 32 pixels from p0 of an LDS image
@@ -172,7 +173,7 @@ __global__ __launch_bounds__(kWideThreads) void k_conv_wgrad(WgradArgs a) {
         step(st[0], 0, p0);
         if (p0 + kPix < p_end) step(st[kStages - 1], 1, p0 + kPix);
     }
-    float *part = a.part + (size_t)blockIdx.z * (rows + 1) * c.cout;
+    float *part = a.w_sums + blockIdx.z * a.split_stride;
 #pragma unroll
     for (int m = 0; m < 2; m++) {
         const int row = row0 + 32 * wave + 16 * m + (lane & 15);
@@ -185,7 +186,7 @@ __global__ __launch_bounds__(kWideThreads) void k_conv_wgrad(WgradArgs a) {
     }
     if (bias && (lane & 15) == 0) {
         const int co = co0 + 16 * wave + 4 * (lane >> 4);
-        if (co < c.cout) store_f4(part + (size_t)rows * c.cout + co, accb);
+        if (co < c.cout) store_f4(a.b_sums + blockIdx.z * a.split_stride + co, accb);
     }
 }
 
@@ -296,7 +297,7 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_conv_wgrad_narrow(WgradAr
         float s = 0.f;
 #pragma unroll
         for (int w = 0; w < kNarrowWaves; w++) s += ((const float *)(lds + w * kWaveBytes))[threadIdx.x];
-        a.part[((size_t)blockIdx.z * (rows + 1) + r) * c.cout + co] = s;
+        (r < rows ? a.w_sums + r * c.cout : a.b_sums)[blockIdx.z * a.split_stride + co] = s;
     }
 }
 
@@ -308,6 +309,7 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_conv_wgrad_narrow(WgradAr
 constexpr int kReduceThreads = 256, kReduceWaves = kReduceThreads / 64, kReduceSums = 16 / kReduceWaves;
 constexpr int kReduceAhead = 2;  // 7 wavefronts a SIMD; 1, 3 and 4: 16.7, 15.7 and 15.5 us for k_conv_update's 15.0
 
+template <int AHEAD>
 __device__ __forceinline__ void sum_splits(const float *part, int64_t count, int splits, int64_t q, bool on,
                                            float4 (*red)[64]) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -315,10 +317,10 @@ __device__ __forceinline__ void sum_splits(const float *part, int64_t count, int
 #pragma unroll
     for (int j = 0; j < kReduceSums; j++) s[j] = make_float4(0.f, 0.f, 0.f, 0.f);
     part += on ? 4 * q : 0;
-    for (int z0 = wave; z0 < splits; z0 += 16 * kReduceAhead) {
-        float4 v[kReduceAhead][kReduceSums];
+    for (int z0 = wave; z0 < splits; z0 += 16 * AHEAD) {
+        float4 v[AHEAD][kReduceSums];
 #pragma unroll
-        for (int u = 0; u < kReduceAhead; u++)
+        for (int u = 0; u < AHEAD; u++)
 #pragma unroll
             for (int j = 0; j < kReduceSums; j++) {
                 const int z = z0 + 16 * u + kReduceWaves * j;
@@ -326,7 +328,7 @@ __device__ __forceinline__ void sum_splits(const float *part, int64_t count, int
                 if (z < splits) v[u][j] = load_f4(part + z * count);
             }
 #pragma unroll
-        for (int u = 0; u < kReduceAhead; u++)
+        for (int u = 0; u < AHEAD; u++)
 #pragma unroll
             for (int j = 0; j < kReduceSums; j++)
                 s[j].x += v[u][j].x, s[j].y += v[u][j].y, s[j].z += v[u][j].z, s[j].w += v[u][j].w;
@@ -344,12 +346,13 @@ __device__ __forceinline__ float ordered_sum(const float4 (*red)[64]) {
     return s;
 }
 
+template <int AHEAD>
 __global__ __launch_bounds__(kReduceThreads) void k_conv_wgrad_reduce(int M, int N, int splits,
                                                                       const float *__restrict__ part,
                                                                       float *__restrict__ dw, float *__restrict__ db) {
     __shared__ float4 red[16][64];
     const int64_t q = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63), count = (int64_t)M * N;  // N is a multiple of 4
-    sum_splits(part, count, splits, q, 4 * q < count, red);
+    sum_splits<AHEAD>(part, count, splits, q, 4 * q < count, red);
     __syncthreads();
     const int64_t i = (int64_t)blockIdx.x * kReduceThreads + threadIdx.x, last = count - N;
     if (i >= count) return;
@@ -375,7 +378,7 @@ __global__ __launch_bounds__(kReduceThreads) void k_conv_update(UpdateArgs a) {
     const float m = a.m[i], v = a.v[i], w0 = a.p[i];
     if (p.sums) {
         const int64_t q = (int64_t)(blockIdx.x - p.block0) * 64 + (threadIdx.x & 63);
-        sum_splits(p.sums, p.n, p.splits, q, 4 * q < p.n, red);
+        sum_splits<kReduceAhead>(p.sums, p.n, p.splits, q, 4 * q < p.n, red);
         __syncthreads();
         g = ordered_sum(red);
     }
@@ -422,9 +425,10 @@ void launch_wide(const WgradArgs &a, dim3 grid, hipStream_t s) {
 int64_t conv_wgt_work_limit(const ConvShape &c) { return (int64_t)split_limit(c) * (9 * c.cin + 1) * c.cout; }
 int64_t conv_wgt_work_floats(const ConvShape &c) { return (int64_t)max_splits(c) * (9 * c.cin + 1) * c.cout; }
 
-ups_status launch_conv_wgrad_sums(const ConvShape &c, const uint16_t *x, const uint16_t *y, const float *dy, float *work,
-                                  int *splits, hipStream_t s) {
-    const int P = c.n * c.ho * c.wo;
+// dw, db: where a single split's sums go, which are the gradients; null: into `work` like the others.
+static ups_status wgrad_sums(const ConvShape &c, const uint16_t *x, const uint16_t *y, const float *dy, float *work,
+                             float *dw, float *db, int *splits, hipStream_t s) {
+    const int P = c.n * c.ho * c.wo, M = 9 * c.cin + 1;
     *splits = 0;
     if (P == 0) return UPS_OK;
     const bool narrow = c.cin <= 3;
@@ -433,8 +437,10 @@ ups_status launch_conv_wgrad_sums(const ConvShape &c, const uint16_t *x, const u
     // channels: 25.7 and 26.6 us against 36.0 and 36.9); 32 where there are no more
     const int nf = narrow || c.cout <= 32 ? 2 : 4;
     const int chunk = cdiv(cdiv(P, max_splits(c)), unit) * unit;
-    const WgradArgs a{walk_args(c, unit), x, y, dy, work, chunk};
     *splits = cdiv(P, chunk);
+    const bool direct = *splits == 1 && dw;
+    const WgradArgs a{walk_args(c, unit), x, y, dy, direct ? dw : work, direct ? db : work + (int64_t)(M - 1) * c.cout,
+                      (int64_t)M * c.cout, chunk};
     const dim3 grid(row_tiles, cdiv(c.cout, 16 * nf), *splits);
     if (c.cin == 1) hipLaunchKernelGGL(k_conv_wgrad_narrow<1>, grid, dim3(64 * kNarrowWaves), 0, s, a);
     else if (c.cin == 2) hipLaunchKernelGGL(k_conv_wgrad_narrow<2>, grid, dim3(64 * kNarrowWaves), 0, s, a);
@@ -445,15 +451,26 @@ ups_status launch_conv_wgrad_sums(const ConvShape &c, const uint16_t *x, const u
     return UPS_OK;
 }
 
+ups_status launch_conv_wgrad_sums(const ConvShape &c, const uint16_t *x, const uint16_t *y, const float *dy, float *work,
+                                  int *splits, hipStream_t s) {
+    return wgrad_sums(c, x, y, dy, work, nullptr, nullptr, splits, s);
+}
+
 ups_status launch_conv_bwd_weight(const ConvShape &c, const uint16_t *x, const uint16_t *y, const float *dy,
                                   float *dw, float *db, float *work, int64_t work_floats, hipStream_t s) {
     const int M = 9 * c.cin + 1;
     UPS_REQUIRE(conv_wgt_work_floats(c) <= work_floats, "weight-gradient workspace too small");
     int splits = 0;
-    const ups_status st = launch_conv_wgrad_sums(c, x, y, dy, work, &splits, s);
-    if (st != UPS_OK) return st;
-    hipLaunchKernelGGL(k_conv_wgrad_reduce, dim3((unsigned)(((int64_t)M * c.cout / 4 + 63) / 64)), dim3(kReduceThreads),
-                       0, s, M, c.cout, splits, work, dw, db);
+    const ups_status st = wgrad_sums(c, x, y, dy, work, dw, db, &splits, s);
+    if (st != UPS_OK || splits == 1) return st;
+    const dim3 blocks((unsigned)(((int64_t)M * c.cout / 4 + 63) / 64));
+    // more than one trip of loads where a CU has no other block: eight splits of a sum in flight, not two (64 x 16 x 64
+    // pixels of 5 -> 8 channels, 256 splits: 12.5 -> 11.8 us)
+    if (blocks.x <= 256 && splits > 16 * kReduceAhead)
+        hipLaunchKernelGGL(k_conv_wgrad_reduce<8>, blocks, dim3(kReduceThreads), 0, s, M, c.cout, splits, work, dw, db);
+    else
+        hipLaunchKernelGGL(k_conv_wgrad_reduce<kReduceAhead>, blocks, dim3(kReduceThreads), 0, s, M, c.cout, splits, work,
+                           dw, db);
     UPS_CHECK_HIP(hipGetLastError());
     return UPS_OK;
 }

@@ -179,6 +179,31 @@ def test_conv_data_gradient_few_channels(gpu_lib, shape):
     test_conv_gather_tile_edges(gpu_lib, shape)
 
 
+@pytest.mark.parametrize("cin", [1, 3, 4, 5, 8, 33])
+@pytest.mark.parametrize("pixels", [1, 63, 64, 65, 512, 513, 4097])
+def test_weight_gradient_of_one_split_and_of_many(gpu_lib, cin, pixels):
+    """Whole numbers whose sums stay below 2^24, so exact, around the pixel counts from which a layer's sums are split
+    (64, and 512 for at most three channels); nothing beside the gradients is written."""
+    import torch
+    r = _rng(900 + 7 * cin + pixels)
+    x = r.integers(0, 4, size=(1, pixels, 2, cin)).astype(np.float64)
+    dy = r.integers(-3, 4, size=(1, (pixels - 1) // 2 + 1, 1, 12)).astype(np.float64)
+    _, dW_ref, db_ref = C.conv_backward(x, np.ones_like(dy), dy, np.zeros((9 * cin, 12)), 2)
+    n_w = 9 * cin * 12
+    out = torch.full((n_w + 12 + 48,), 7.0, dtype=torch.float32, device="cuda")
+    dW, db = out[16:16 + n_w], out[32 + n_w:44 + n_w]
+    n = int(gpu_lib.load().ups_conv3x3_backward_weight_work(1, pixels, 2, cin, 12, 2))
+    work = torch.full((n,), float("nan"), dtype=torch.float32, device="cuda")
+    xb, yb, g = _bf(x), _bf(np.ones_like(dy)), _f32(dy)
+    p = gpu_lib._P
+    gpu_lib._check(gpu_lib.load().ups_conv3x3_backward_weight(
+        1, pixels, 2, cin, 12, 2, p(xb.data_ptr()), p(yb.data_ptr()), p(g.data_ptr()), p(dW.data_ptr()),
+        p(db.data_ptr()), p(work.data_ptr()), n, gpu_lib._stream()))
+    assert np.array_equal(_np(dW), dW_ref.ravel()) and np.array_equal(_np(db), db_ref)
+    rest = torch.cat([out[:16], out[16 + n_w:32 + n_w], out[44 + n_w:]])
+    assert bool((rest == 7.0).all())
+
+
 def test_conv_empty_batch(gpu_lib):
     import torch
     x = torch.zeros((0, 8, 16, 4), dtype=torch.bfloat16, device="cuda")
