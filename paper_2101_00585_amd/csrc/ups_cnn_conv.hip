@@ -543,10 +543,13 @@ ups_status launch_conv_narrow_fwd(const ConvShape &c, const uint16_t *x, const u
         UPS_CHECK_HIP(hipGetLastError());
         return UPS_OK;
     }
-    // at most five blocks a CU (what the registers leave room for at three channels), each wavefront several groups
-    const int P = c.n * c.ho * c.wo, blocks = std::max(1, std::min(1280, (P + 127) / 128));
+    // at most five blocks a CU (what the registers leave room for at three channels), each wavefront several groups; at
+    // three channels at most two rounds of them over all output channels (131072 pixels, 128 and 256 channels: 25.8 and
+    // 46.7 us with 1280 for every 32 channels, 21.5 and 30.6 so; at one and two channels the same or up to 16 % slower)
+    const int P = c.n * c.ho * c.wo, ny = (c.cout + 31) / 32;
+    const int blocks = std::max(1, std::min(1280 / (c.cin == 3 ? std::max(1, ny / 2) : 1), (P + 127) / 128));
     const WalkArgs a = walk_args(c, 64 * blocks);
-    const dim3 grid(blocks, (c.cout + 31) / 32), block(256);
+    const dim3 grid(blocks, ny), block(256);
     if (c.cin == 1) hipLaunchKernelGGL(k_conv_fwd_narrow<1>, grid, block, 0, s, a, x, w_nk, b, y);
     else if (c.cin == 2) hipLaunchKernelGGL(k_conv_fwd_narrow<2>, grid, block, 0, s, a, x, w_nk, b, y);
     else hipLaunchKernelGGL(k_conv_fwd_narrow<3>, grid, block, 0, s, a, x, w_nk, b, y);

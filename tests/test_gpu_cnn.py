@@ -179,6 +179,11 @@ def test_conv_data_gradient_few_channels(gpu_lib, shape):
     test_conv_gather_tile_edges(gpu_lib, shape)
 
 
+def test_conv_forward_three_channels_many_outputs(gpu_lib):
+    """More output channels and pixels than two rounds of blocks take in one group of pixels a wavefront."""
+    test_conv_gather_tile_edges(gpu_lib, (43, 31, 64, 3, 132, 1))
+
+
 @pytest.mark.parametrize("cin", [1, 3, 4, 5, 8, 33])
 @pytest.mark.parametrize("pixels", [1, 63, 64, 65, 512, 513, 4097])
 def test_weight_gradient_of_one_split_and_of_many(gpu_lib, cin, pixels):
