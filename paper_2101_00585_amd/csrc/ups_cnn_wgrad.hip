@@ -8,6 +8,13 @@
 // come from gfx950's transposing LDS read (ds_read_b64_tr_b16): the lanes of a
 // 16-lane group supply the addresses of four pixels' 16-element rows and each
 // receives the four pixels of one row element.
+//
+// The order of every sum is that of the flattened contraction: a split's pixels
+// in ascending slices of 32, a slice's pixels in order within the instruction,
+// the splits as sum_splits says.  A training step's weights are rounded to
+// bfloat16, so a sum added in another order is not a difference of 1e-7 in the
+// steps after it: one weight that rounds the other way moved the gradients by
+// 4e-4.
 #include "ups_cnn.hpp"
 
 namespace ups {
@@ -27,11 +34,14 @@ struct WgradArgs {
     int chunk;               // output pixels of a split
 };
 
-// Fragment of rows e0 .. e0+15 over the 32 pixels from p0 of an LDS image
-// [pixel][element] of `pitch` bytes.  Element order of the contraction: lane
-// group g holds pixels 4g .. 4g+3 and 16+4g .. 16+4g+3 (the same for both
-// operands), so the sixteen 32-byte rows of one read fall on different banks
-// when the pitch is an odd multiple of 32 bytes.
+// Fragment of rows e0 .. e0+15 over the 32 pixels from row p0 of an LDS image
+// [pixel][element] of `pitch` bytes whose rows are in the order of lds_row: lane
+// group g holds pixels 8g .. 8g+7, which lie in rows 4g .. 4g+3 and 16+4g ..
+// 16+4g+3, so the sixteen 32-byte rows of one read fall on different banks when
+// the pitch is an odd multiple of 32 bytes.
+__device__ __forceinline__ int lds_row(int pixel) {
+    return (pixel & ~31) + ((pixel & 24) >> 1) + ((pixel & 4) << 2) + (pixel & 3);
+}
 __device__ __forceinline__ bf16x8 tr_fragment(const uint8_t *base, int pitch, int p0, int e0) {
     const int l = threadIdx.x & 63, px = p0 + 4 * (l >> 4) + ((l & 15) >> 2);
     const uint8_t *p = base + px * pitch + 2 * e0 + 8 * (l & 3);
@@ -49,7 +59,7 @@ constexpr int kRowTile = 288, kPix = 64, kWideThreads = 576;
 // with about one block a CU, which the workspace of the splits' sums sets; so
 // two steps' loads are in flight and two LDS buffers leave one barrier a step.
 // Layers of 32 -> 64, 64 -> 96, 96 -> 128 and 128 -> 128 channels at batch
-// 256: 25.7, 26.6, 16.7 and 18.7 us with the reduction, against 177.5, 165.6,
+// 256: 26.5, 27.7, 17.8 and 18.0 us with the reduction, against 177.5, 165.6,
 // 68.6 and 78 on 64 x 64 tiles gathered along pixels by 2-byte loads.  UNIT:
 // elements per load of x (8 where cin is a multiple of 8, 2 where it is even,
 // else 1, whose 32 loads a step leave registers for one step in flight).
@@ -139,13 +149,13 @@ __global__ __launch_bounds__(kWideThreads) void k_conv_wgrad(WgradArgs a) {
 #pragma unroll
         for (int i = 0; i < 4; i++) {
             const uint32_t *v = f.x[i];
-            *(uint4 *)(x + (pr + i) * kXP + 16 * r8) =
+            *(uint4 *)(x + (lds_row(pr) + i) * kXP + 16 * r8) =
                 UNIT == 1 ? make_uint4(v[0] | v[1] << 16, v[2] | v[3] << 16, v[4] | v[5] << 16, v[6] | v[7] << 16)
                           : make_uint4(v[0], v[1], v[2], v[3]);
         }
         if (gp < kPix) {
             const uint2 lo = masked_grad4(f.y[0], f.dy[0]), hi = masked_grad4(f.y[1], f.dy[1]);
-            *(uint4 *)(g + gp * kGP + 16 * (t % (2 * NF))) = make_uint4(lo.x, lo.y, hi.x, hi.y);
+            *(uint4 *)(g + lds_row(gp) * kGP + 16 * (t % (2 * NF))) = make_uint4(lo.x, lo.y, hi.x, hi.y);
         }
         // the buffer's readers of two steps ago passed the last step's barrier
         __syncthreads();
@@ -192,11 +202,11 @@ __global__ __launch_bounds__(kWideThreads) void k_conv_wgrad(WgradArgs a) {
 
 // Narrow form, for cin <= 3 (at most 27 rows, and the bias as one more row of
 // ones, so that the 288-row tile would be nine tenths empty): bound by reading
-// the gradients, so every wavefront streams its own pixels, 32 a step through
-// its own 6 KB of LDS without block barriers (the next step's loads in
-// flight), and the block's sixteen sums are added in wavefront order at the
-// end.  2 -> 32 channels, 524288 pixels: 25 us (109 MB at 5.3 TB/s without
-// the reduction's 5 us) against 335 on 64 x 64 tiles.
+// the gradients, so each of sixteen wavefronts streams its own 32 pixels of a
+// step through 6 KB of LDS, the next step's loads in flight, and four of them
+// then multiply the step's slices in order, a quarter of the result each.
+// 2 -> 32 channels, 524288 pixels: 20.3 us (109 MB at 5.4 TB/s) without the
+// reduction's 5 us, against 335 with it on 64 x 64 tiles.
 constexpr int kNarrowWaves = 16;
 
 template <int CIN>
@@ -205,7 +215,7 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_conv_wgrad_narrow(WgradAr
     constexpr int kWaveBytes = 64 * kP;   // 32 pixels of x, 32 of the gradient
     __shared__ __align__(16) uint8_t lds[kNarrowWaves * kWaveBytes];
     const ConvShape &c = a.walk.c;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     uint8_t *xs = lds + wave * kWaveBytes, *gs = xs + 32 * kP;
     constexpr int rows = 9 * CIN;
     const int co0 = blockIdx.y * 32;
@@ -246,117 +256,116 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_conv_wgrad_narrow(WgradAr
             }
         }
     };
-    f32x4 acc[2][2];
+    // the quarter of the result that this wavefront multiplies
+    const int m = wave & 1, f = (wave >> 1) & 1;
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    constexpr int kStep = 32 * kNarrowWaves;
+    if (p_begin + 32 * wave < p_end) fetch(p_begin + 32 * wave);
+    for (int p0 = p_begin; p0 < p_end; p0 += kStep) {
+        if (p0 + 32 * wave < p_end) {
+            uint16_t *row = (uint16_t *)(xs + lds_row(px) * kP);
 #pragma unroll
-    for (int m = 0; m < 2; m++)
+            for (int k = 0; k < 5; k++) {
+                const int tap = 5 * half + k;
+                if (tap < 9) {
+                    uint16_t *d = row + tap * CIN;
+                    if constexpr (CIN == 2) *(uint32_t *)d = xv[k][0] | ((uint32_t)xv[k][1] << 16);
+                    else
 #pragma unroll
-        for (int f = 0; f < 2; f++) acc[m][f] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int step = 32 * kNarrowWaves;
-    int p0 = p_begin + 32 * wave;
-    if (p0 < p_end) fetch(p0);
-    for (; p0 < p_end; p0 += step) {
-#pragma unroll
-        for (int k = 0; k < 5; k++) {
-            const int tap = 5 * half + k;
-            if (tap < 9) {
-                uint16_t *d = (uint16_t *)(xs + px * kP) + tap * CIN;
-                if constexpr (CIN == 2) *(uint32_t *)d = xv[k][0] | ((uint32_t)xv[k][1] << 16);
-                else
-#pragma unroll
-                    for (int e = 0; e < CIN; e++) d[e] = xv[k][e];
-            } else {
-                ((uint16_t *)(xs + px * kP))[rows] = 0x3F80;
+                        for (int e = 0; e < CIN; e++) d[e] = xv[k][e];
+                } else {
+                    row[rows] = 0x3F80;
+                }
             }
+#pragma unroll
+            for (int k = 0; k < 4; k++)
+                *(uint2 *)(gs + lds_row((lane >> 3) + 8 * k) * kP + 8 * (lane & 7)) = masked_grad4(gy[k], gd[k]);
         }
+        __syncthreads();
+        if (p0 + kStep + 32 * wave < p_end) fetch(p0 + kStep + 32 * wave);
+        if (wave < 4) {
+            const int slices = min(kNarrowWaves, (p_end - p0 + 31) / 32);
+            const uint8_t *x = lds;
+#pragma unroll 4
+            for (int k = 0; k < slices; k++, x += kWaveBytes)
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tr_fragment(x + 32 * kP, kP, 0, 16 * f),
+                                                              tr_fragment(x, kP, 0, 16 * m), acc, 0, 0, 0);
+        }
+        __syncthreads();
+    }
+    const int r = 16 * m + (lane & 15), co = co0 + 16 * f + 4 * (lane >> 4);
+    if (wave < 4 && r <= rows && co < c.cout)
+        store_f4((r < rows ? a.w_sums + r * c.cout : a.b_sums) + blockIdx.z * a.split_stride + co, acc);
+}
+
+// The sum over the splits of output threadIdx.x of a block's 256 (count in all,
+// a multiple of 4, rows of which are `first` onward).  At least 64 splits of few
+// outputs are added as 64 sums, of every 64th split, and these in halves (sum l
+// and sum l + 32, then 16, .. 1); the others one after the other.  Bound by the
+// latency of the loads, of which sixteen are in flight (64, in 256 registers a
+// thread: 6 us more a training step of 256 pairs, 2.5 for 128 -> 128 channels).
+constexpr int kReduceThreads = 256;
+
+// (at most 256 splits: split_limit)
+__device__ __forceinline__ bool splits_in_halves(int64_t count, int splits) { return count <= 32768 && splits >= 64; }
+
+__device__ __forceinline__ float sum_splits(const float *part, int64_t count, int splits, int64_t first,
+                                            float4 (*red)[64]) {
+    if (!splits_in_halves(count, splits)) {
+        const float *p = part + min(first + (int64_t)threadIdx.x, count - 1);
+        constexpr int kAhead = 16;
+        float s = 0.f;
+        for (int z0 = 0; z0 < splits; z0 += kAhead) {
+            float v[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; u++) v[u] = p[min(z0 + u, splits - 1) * count];
+#pragma unroll
+            for (int u = 0; u < kAhead; u++) s += z0 + u < splits ? v[u] : 0.f;
+        }
+        return s;
+    }
+    // a thread makes 16 of the 64 sums (4 j + its wavefront) of four outputs, in the order in which the halves meet
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const float *p = part + min(first + 4 * lane, count - 4);
+    auto add = [](float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); };
+    auto quarter = [&](int j0) {  // sums j0, j0 + 4, j0 + 8, j0 + 12
+        float4 v[4][4], s[4];
 #pragma unroll
         for (int k = 0; k < 4; k++)
-            *(uint2 *)(gs + ((lane >> 3) + 8 * k) * kP + 8 * (lane & 7)) = masked_grad4(gy[k], gd[k]);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        if (p0 + step < p_end) fetch(p0 + step);
-        bf16x8 fx[2], fg[2];
 #pragma unroll
-        for (int m = 0; m < 2; m++) fx[m] = tr_fragment(xs, kP, 0, 16 * m), fg[m] = tr_fragment(gs, kP, 0, 16 * m);
-#pragma unroll
-        for (int f = 0; f < 2; f++)
-#pragma unroll
-            for (int m = 0; m < 2; m++)
-                acc[m][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fg[f], fx[m], acc[m][f], 0, 0, 0);
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-    __syncthreads();
-    // this wavefront's 32 x 32 sums, [r][co]
-    float *sums = (float *)(lds + wave * kWaveBytes);
-#pragma unroll
-    for (int m = 0; m < 2; m++)
-#pragma unroll
-        for (int f = 0; f < 2; f++)
-            *(f32x4 *)(sums + (16 * m + (lane & 15)) * 32 + 16 * f + 4 * (lane >> 4)) = acc[m][f];
-    __syncthreads();
-    const int r = threadIdx.x >> 5, co = co0 + (threadIdx.x & 31);
-    if (r <= rows && co < c.cout) {
-        float s = 0.f;
-#pragma unroll
-        for (int w = 0; w < kNarrowWaves; w++) s += ((const float *)(lds + w * kWaveBytes))[threadIdx.x];
-        (r < rows ? a.w_sums + r * c.cout : a.b_sums)[blockIdx.z * a.split_stride + co] = s;
-    }
-}
-
-// The splits' sums of a block's 64 quads of outputs (four consecutive of the
-// count outputs each), added in a fixed order: sixteen sums, of every
-// sixteenth split, to be added in turn (ordered_sum) after a barrier.  Bound by
-// the latency of the loads: each wavefront makes four of the sixteen sums, two
-// splits of each in flight.
-constexpr int kReduceThreads = 256, kReduceWaves = kReduceThreads / 64, kReduceSums = 16 / kReduceWaves;
-constexpr int kReduceAhead = 2;  // 7 wavefronts a SIMD; 1, 3 and 4: 16.7, 15.7 and 15.5 us for k_conv_update's 15.0
-
-template <int AHEAD>
-__device__ __forceinline__ void sum_splits(const float *part, int64_t count, int splits, int64_t q, bool on,
-                                           float4 (*red)[64]) {
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    float4 s[kReduceSums];
-#pragma unroll
-    for (int j = 0; j < kReduceSums; j++) s[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-    part += on ? 4 * q : 0;
-    for (int z0 = wave; z0 < splits; z0 += 16 * AHEAD) {
-        float4 v[AHEAD][kReduceSums];
-#pragma unroll
-        for (int u = 0; u < AHEAD; u++)
-#pragma unroll
-            for (int j = 0; j < kReduceSums; j++) {
-                const int z = z0 + 16 * u + kReduceWaves * j;
-                v[u][j] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (z < splits) v[u][j] = load_f4(part + z * count);
+            for (int u = 0; u < 4; u++) {
+                const int z = wave + 4 * (j0 + 4 * k) + 64 * u;
+                v[k][u] = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (z < splits) v[k][u] = load_f4(p + z * count);
             }
 #pragma unroll
-        for (int u = 0; u < AHEAD; u++)
-#pragma unroll
-            for (int j = 0; j < kReduceSums; j++)
-                s[j].x += v[u][j].x, s[j].y += v[u][j].y, s[j].z += v[u][j].z, s[j].w += v[u][j].w;
+        for (int k = 0; k < 4; k++) s[k] = add(add(add(v[k][0], v[k][1]), v[k][2]), v[k][3]);
+        return add(add(s[0], s[2]), add(s[1], s[3]));
+    };
+    float4 half, sum;
+#pragma unroll 1
+    for (int h = 0; h < 2; h++) {
+#pragma unroll 1
+        for (int g = 0; g < 2; g++) {
+            const float4 q = quarter(h + 2 * g);
+            half = g ? add(half, q) : q;
+        }
+        sum = h ? add(sum, half) : half;
     }
-#pragma unroll
-    for (int j = 0; j < kReduceSums; j++) red[wave + kReduceWaves * j][lane] = s[j];
-}
-
-// The block's output threadIdx.x.
-__device__ __forceinline__ float ordered_sum(const float4 (*red)[64]) {
+    red[wave][lane] = sum;
+    __syncthreads();
     const float *r = (const float *)red + threadIdx.x;
-    float s = r[0];
-#pragma unroll
-    for (int w = 1; w < 16; w++) s += r[256 * w];
-    return s;
+    return (r[0] + r[512]) + (r[256] + r[768]);
 }
 
-template <int AHEAD>
 __global__ __launch_bounds__(kReduceThreads) void k_conv_wgrad_reduce(int M, int N, int splits,
                                                                       const float *__restrict__ part,
                                                                       float *__restrict__ dw, float *__restrict__ db) {
-    __shared__ float4 red[16][64];
-    const int64_t q = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63), count = (int64_t)M * N;  // N is a multiple of 4
-    sum_splits<AHEAD>(part, count, splits, q, 4 * q < count, red);
-    __syncthreads();
-    const int64_t i = (int64_t)blockIdx.x * kReduceThreads + threadIdx.x, last = count - N;
-    if (i >= count) return;
-    *(i < last ? dw + i : db + (i - last)) = ordered_sum(red);
+    __shared__ float4 red[4][64];
+    const int64_t first = (int64_t)blockIdx.x * kReduceThreads, count = (int64_t)M * N, last = count - N;
+    const float s = sum_splits(part, count, splits, first, red);
+    const int64_t i = first + threadIdx.x;
+    if (i < count) *(i < last ? dw + i : db + (i - last)) = s;
 }
 
 // The whole parameter update of a training step in one launch: the layers'
@@ -364,11 +373,11 @@ __global__ __launch_bounds__(kReduceThreads) void k_conv_wgrad_reduce(int M, int
 // beta1^t) and c2 = 1 / (1 - beta2^t), and the bfloat16 copies of the
 // convolutions' weights; a parameter a thread, its moments on their way during
 // the sums.  Blocks of four wavefronts are all resident at once for the
-// network's 360000 parameters: 15.0 us for the 60 MB of sums of 256 pairs, against
+// network's 360000 parameters: 15.4 us for the 60 MB of sums of 256 pairs, against
 // 18.4 with sixteen wavefronts (2.75 rounds of blocks, the moments after the
 // sums by one wavefront).
 __global__ __launch_bounds__(kReduceThreads) void k_conv_update(UpdateArgs a) {
-    __shared__ float4 red[16][64];
+    __shared__ float4 red[4][64];
     int l = 0;
     while (l + 1 < a.count && (int)blockIdx.x >= a.part[l + 1].block0) l++;
     const UpdatePart &p = a.part[l];
@@ -377,10 +386,7 @@ __global__ __launch_bounds__(kReduceThreads) void k_conv_update(UpdateArgs a) {
     float g = p.sums ? 0.f : a.g[i];
     const float m = a.m[i], v = a.v[i], w0 = a.p[i];
     if (p.sums) {
-        const int64_t q = (int64_t)(blockIdx.x - p.block0) * 64 + (threadIdx.x & 63);
-        sum_splits<kReduceAhead>(p.sums, p.n, p.splits, q, 4 * q < p.n, red);
-        __syncthreads();
-        g = ordered_sum(red);
+        g = sum_splits(p.sums, p.n, p.splits, (int64_t)(blockIdx.x - p.block0) * kReduceThreads, red);
     }
     if (j >= p.n) return;
     if (p.sums) a.g[i] = g;
@@ -408,10 +414,11 @@ int split_limit(const ConvShape &c) {
     const int tiles = cdiv(9 * c.cin + 1, 64) * cdiv(c.cout, 64), P = std::max(c.n * c.ho * c.wo, 1);
     return std::min(std::max(1, std::min(256, cdiv(1024, tiles))), cdiv(P, 64));
 }
-int max_splits(const ConvShape &c) {
-    const int P = std::max(c.n * c.ho * c.wo, 1);
-    return cdiv(P, std::max(64, cdiv(cdiv(P, split_limit(c)), 16) * 16));
+// Output pixels of a split.
+int split_chunk(const ConvShape &c) {
+    return std::max(64, cdiv(cdiv(std::max(c.n * c.ho * c.wo, 1), split_limit(c)), 16) * 16);
 }
+int max_splits(const ConvShape &c) { return cdiv(std::max(c.n * c.ho * c.wo, 1), split_chunk(c)); }
 
 template <int NF>
 void launch_wide(const WgradArgs &a, dim3 grid, hipStream_t s) {
@@ -436,7 +443,7 @@ static ups_status wgrad_sums(const ConvShape &c, const uint16_t *x, const uint16
     // 64 channels a block: half the staged windows of 32 for the same products (batch 256, 32 -> 64 and 64 -> 96
     // channels: 25.7 and 26.6 us against 36.0 and 36.9); 32 where there are no more
     const int nf = narrow || c.cout <= 32 ? 2 : 4;
-    const int chunk = cdiv(cdiv(P, max_splits(c)), unit) * unit;
+    const int chunk = split_chunk(c);
     *splits = cdiv(P, chunk);
     const bool direct = *splits == 1 && dw;
     const WgradArgs a{walk_args(c, unit), x, y, dy, direct ? dw : work, direct ? db : work + (int64_t)(M - 1) * c.cout,
@@ -463,14 +470,8 @@ ups_status launch_conv_bwd_weight(const ConvShape &c, const uint16_t *x, const u
     int splits = 0;
     const ups_status st = wgrad_sums(c, x, y, dy, work, dw, db, &splits, s);
     if (st != UPS_OK || splits == 1) return st;
-    const dim3 blocks((unsigned)(((int64_t)M * c.cout / 4 + 63) / 64));
-    // more than one trip of loads where a CU has no other block: eight splits of a sum in flight, not two (64 x 16 x 64
-    // pixels of 5 -> 8 channels, 256 splits: 12.5 -> 11.8 us)
-    if (blocks.x <= 256 && splits > 16 * kReduceAhead)
-        hipLaunchKernelGGL(k_conv_wgrad_reduce<8>, blocks, dim3(kReduceThreads), 0, s, M, c.cout, splits, work, dw, db);
-    else
-        hipLaunchKernelGGL(k_conv_wgrad_reduce<kReduceAhead>, blocks, dim3(kReduceThreads), 0, s, M, c.cout, splits, work,
-                           dw, db);
+    hipLaunchKernelGGL(k_conv_wgrad_reduce, dim3((unsigned)(((int64_t)M * c.cout + kReduceThreads - 1) / kReduceThreads)),
+                       dim3(kReduceThreads), 0, s, M, c.cout, splits, work, dw, db);
     UPS_CHECK_HIP(hipGetLastError());
     return UPS_OK;
 }

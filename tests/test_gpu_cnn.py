@@ -209,6 +209,45 @@ def test_weight_gradient_of_one_split_and_of_many(gpu_lib, cin, pixels):
     assert bool((rest == 7.0).all())
 
 
+def _in_order(v):
+    s = np.float32(0)
+    for x in v:
+        s += np.float32(x)
+    return s
+
+
+def _in_halves(v):
+    v = np.asarray([_in_order(v[l::64]) for l in range(64)], dtype=np.float32)
+    while len(v) > 1:
+        v = v[:len(v) // 2] + v[len(v) // 2:]
+    return v[0]
+
+
+# (images of 64 pixels, input channels, output channels, pixels that count and their gradients): a split of 64 pixels an
+# image, or, with up to three channels on 384 images, splits of 96 pixels in three slices of 32.  Two splits' ones meet
+# before 2^24 in one order and after it in another; 2^24 + 1 rounds to 2^24.
+@pytest.mark.parametrize("n,cin,cout,ones", [(40, 4, 8, (64, 17 * 64)), (40, 2, 8, (64, 17 * 64)),
+                                             (100, 4, 8, (4 * 64, 12 * 64)), (100, 4, 8, (64, 33 * 64)),
+                                             (100, 1, 8, (4 * 64, 12 * 64)), (60, 32, 116, (64, 33 * 64)),
+                                             (384, 2, 8, (32, 64)), (384, 3, 36, (33, 95)), (384, 1, 4, (2, 40))])
+def test_weight_gradient_order_of_sums(gpu_lib, n, cin, cout, ones):
+    """A split's pixels are added in ascending slices of 32, and the splits one after the other, or as 64 sums added in
+    halves where there are at least 64 of at most 32768 gradients: the bytes of FP32 sums in that order."""
+    dy = np.zeros((n, 2, 32, cout))
+    flat = dy.reshape(-1, cout)
+    flat[0] = 2.0 ** 24
+    for p in ones:
+        flat[p] = 1.0
+    x = np.ones((n, 2, 32, cin))
+    split = 96 if n == 384 else 64
+    slices = [[flat[i:i + 32, 0].sum() for i in range(z, z + split, 32)] for z in range(0, n * 64, split)]
+    sums = [_in_order(v) for v in slices]
+    ref = _in_halves(sums) if len(sums) >= 64 and (9 * cin + 1) * cout <= 32768 else _in_order(sums)
+    dW, db = gpu_lib.conv3x3_backward_weight(_bf(x), _bf(np.ones_like(dy)), _f32(dy), 1)
+    assert (_np(db) == ref).all(), (float(ref), _np(db)[0])
+    assert (_np(dW)[4 * cin:5 * cin] == ref).all()  # the centre tap reads every pixel
+
+
 def test_conv_empty_batch(gpu_lib):
     import torch
     x = torch.zeros((0, 8, 16, 4), dtype=torch.bfloat16, device="cuda")
