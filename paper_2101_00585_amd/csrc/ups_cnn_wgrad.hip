@@ -202,18 +202,16 @@ __global__ __launch_bounds__(kWideThreads) void k_conv_wgrad(WgradArgs a) {
 
 // Narrow form, for cin <= 3 (at most 27 rows, and the bias as one more row of
 // ones, so that the 288-row tile would be nine tenths empty): bound by reading
-// the gradients, so each of sixteen wavefronts streams its own 32 pixels of a
-// step through 6 KB of LDS, the next step's loads in flight, and four of them
-// then multiply the step's slices in order, a quarter of the result each.
-// 2 -> 32 channels, 524288 pixels: 20.3 us (109 MB at 5.4 TB/s) without the
-// reduction's 5 us, against 335 with it on 64 x 64 tiles.
-constexpr int kNarrowWaves = 16;
-
-template <int CIN>
-__global__ __launch_bounds__(64 * kNarrowWaves) void k_conv_wgrad_narrow(WgradArgs a) {
+// the gradients, so each wavefront streams its own 32 pixels of a step through
+// 6 KB of LDS, the next step's loads in flight, and four of them then multiply
+// the step's slices in order, a quarter of the result each.  2 -> 32 channels,
+// 524288 pixels: 20.3 us (109 MB at 5.4 TB/s) without the reduction's 5 us,
+// against 335 with it on 64 x 64 tiles.
+template <int CIN, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_conv_wgrad_narrow(WgradArgs a) {
     constexpr int kP = 96;                // bytes per pixel: 32 elements, an odd multiple of 32
     constexpr int kWaveBytes = 64 * kP;   // 32 pixels of x, 32 of the gradient
-    __shared__ __align__(16) uint8_t lds[kNarrowWaves * kWaveBytes];
+    __shared__ __align__(16) uint8_t lds[WAVES * kWaveBytes];
     const ConvShape &c = a.walk.c;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     uint8_t *xs = lds + wave * kWaveBytes, *gs = xs + 32 * kP;
@@ -259,7 +257,7 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_conv_wgrad_narrow(WgradAr
     // the quarter of the result that this wavefront multiplies
     const int m = wave & 1, f = (wave >> 1) & 1;
     f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-    constexpr int kStep = 32 * kNarrowWaves;
+    constexpr int kStep = 32 * WAVES;
     if (p_begin + 32 * wave < p_end) fetch(p_begin + 32 * wave);
     for (int p0 = p_begin; p0 < p_end; p0 += kStep) {
         if (p0 + 32 * wave < p_end) {
@@ -283,8 +281,8 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void k_conv_wgrad_narrow(WgradAr
         }
         __syncthreads();
         if (p0 + kStep + 32 * wave < p_end) fetch(p0 + kStep + 32 * wave);
-        if (wave < 4) {
-            const int slices = min(kNarrowWaves, (p_end - p0 + 31) / 32);
+        if (WAVES == 4 || wave < 4) {
+            const int slices = min(WAVES, (p_end - p0 + 31) / 32);
             const uint8_t *x = lds;
 #pragma unroll 4
             for (int k = 0; k < slices; k++, x += kWaveBytes)
@@ -420,6 +418,13 @@ int split_chunk(const ConvShape &c) {
 }
 int max_splits(const ConvShape &c) { return cdiv(std::max(c.n * c.ho * c.wo, 1), split_chunk(c)); }
 
+template <int WAVES>
+void launch_narrow(const WgradArgs &a, dim3 grid, hipStream_t s) {
+    if (a.walk.c.cin == 1) hipLaunchKernelGGL((k_conv_wgrad_narrow<1, WAVES>), grid, dim3(64 * WAVES), 0, s, a);
+    else if (a.walk.c.cin == 2) hipLaunchKernelGGL((k_conv_wgrad_narrow<2, WAVES>), grid, dim3(64 * WAVES), 0, s, a);
+    else hipLaunchKernelGGL((k_conv_wgrad_narrow<3, WAVES>), grid, dim3(64 * WAVES), 0, s, a);
+}
+
 template <int NF>
 void launch_wide(const WgradArgs &a, dim3 grid, hipStream_t s) {
     if (a.walk.c.cin % 8 == 0) hipLaunchKernelGGL((k_conv_wgrad<NF, 8>), grid, dim3(kWideThreads), 0, s, a);
@@ -439,19 +444,22 @@ static ups_status wgrad_sums(const ConvShape &c, const uint16_t *x, const uint16
     *splits = 0;
     if (P == 0) return UPS_OK;
     const bool narrow = c.cin <= 3;
-    const int unit = narrow ? 32 * kNarrowWaves : kPix, row_tiles = narrow ? 1 : cdiv(9 * c.cin, kRowTile);
+    const int row_tiles = narrow ? 1 : cdiv(9 * c.cin, kRowTile);
     // 64 channels a block: half the staged windows of 32 for the same products (batch 256, 32 -> 64 and 64 -> 96
     // channels: 25.7 and 26.6 us against 36.0 and 36.9); 32 where there are no more
     const int nf = narrow || c.cout <= 32 ? 2 : 4;
     const int chunk = split_chunk(c);
+    // narrow form: four wavefronts a block where a split is one step of theirs, or where several blocks share a split
+    // and so a CU (us with 4 / 16, two channels: 16384 pixels to 32 and 128 channels 10.0/10.3 and 12.1/19.0, 131072
+    // pixels 14.6/13.6 and 29.4/35.9)
+    const int waves = chunk <= 128 || c.cout > 32 ? 4 : 16, unit = narrow ? 32 * waves : kPix;
     *splits = cdiv(P, chunk);
     const bool direct = *splits == 1 && dw;
     const WgradArgs a{walk_args(c, unit), x, y, dy, direct ? dw : work, direct ? db : work + (int64_t)(M - 1) * c.cout,
                       (int64_t)M * c.cout, chunk};
     const dim3 grid(row_tiles, cdiv(c.cout, 16 * nf), *splits);
-    if (c.cin == 1) hipLaunchKernelGGL(k_conv_wgrad_narrow<1>, grid, dim3(64 * kNarrowWaves), 0, s, a);
-    else if (c.cin == 2) hipLaunchKernelGGL(k_conv_wgrad_narrow<2>, grid, dim3(64 * kNarrowWaves), 0, s, a);
-    else if (c.cin == 3) hipLaunchKernelGGL(k_conv_wgrad_narrow<3>, grid, dim3(64 * kNarrowWaves), 0, s, a);
+    if (narrow && waves == 4) launch_narrow<4>(a, grid, s);
+    else if (narrow) launch_narrow<16>(a, grid, s);
     else if (nf == 2) launch_wide<2>(a, grid, s);
     else launch_wide<4>(a, grid, s);
     UPS_CHECK_HIP(hipGetLastError());
