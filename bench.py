@@ -49,9 +49,9 @@ HBM_PEAK_GBS = 8000.0
 # device copy in the same runs (FETCH_SIZE reads half the copy's bytes).  The
 # figures and commands are in profiles/icp_iteration_*.md; they hold only for
 # the kernel sources they were taken on (TRAFFIC_SRC_HASH), else traffic is null.
-FETCH_SCALE, WRITE_SCALE = 262144.0 / 131088.75, 1.0
-TRAFFIC_KIB = {"single": (2081.95, 58.20), "batch": (496323.38, 1165.04)}
-TRAFFIC_SRC_HASH = "abac6a9f2da09e00"
+FETCH_SCALE, WRITE_SCALE = 262144.0 / 131093.0, 1.0
+TRAFFIC_KIB = {"single": (2081.95, 58.20), "batch": (496480.58, 1151.51)}
+TRAFFIC_SRC_HASH = "27b8c54a5161d275"
 TRAFFIC_SRC = ("ups_icp_kernels.hpp", "ups_icp_iter_one.hip", "ups_icp_iter_batch.hip",
                "ups_icp_iter_batch_fused.hip", "ups_icp.hpp", "ups_device.hpp", "ups_internal.hpp")
 

@@ -13,9 +13,9 @@
 // index, 32 channels to an instruction.
 //
 // Batch 256, each layer's pass on 64 x 64 tiles (ups_cnn.hip) -> here, us:
-//   channels, stride   2->32,2   32->64,2   64->96,2   96->128,2   128->128,1
-//   forward            30.5->15  28.1->16.7 24.8->12.3 23.0->9.0   28.2->10.5
-//   data gradient                155->29.8  79.9->18.3 52.0->11.2  42.2->14.4
+//   channels, stride   2->32,2    32->64,2   64->96,2   96->128,2   128->128,1
+//   forward            30.5->11.2 28.1->14.9 24.8->11.4 23.0->8.9   28.2->10.4
+//   data gradient                 155->29.8  79.9->17.7 52.0->11.5  42.2->14.5
 // The first layers move 42 and 50 MB forward (8 and 10 us of a device copy);
 // the last are bound by a wavefront's chain of round trips.
 #include "ups_cnn.hpp"
@@ -525,8 +525,9 @@ ups_status launch_conv_gather_fwd(const ConvShape &c, const uint16_t *x, const u
     const GatherArgs a{c, c.h, c.w, c.cin, (c.cin + 31) / 32, c.cout, 9 * c.cin, c.cin, x, nullptr, w_nk, b, y};
     const int M = c.n * c.ho * c.wo;
     // tiles of 256 pixels share a block's weights among eight wavefronts and give each weight fragment two uses, where
-    // they still cover every CU (32 -> 64 channels: 16.7 us, against 20.3 with four wavefronts, three blocks a CU and
-    // so a second round of them); else tiles of 64 pixels (96 -> 128 channels, 8192 pixels: 9.0 us)
+    // they still cover every CU (32 -> 64 channels: 14.9 us; before the output tiles' order 16.7, and 20.3 with four
+    // wavefronts, three blocks a CU and so a second round of them); else tiles of 64 pixels (96 -> 128 channels, 8192
+    // pixels: 8.9 us)
     if (a.N > 32 && M / 256 * ((a.N + 63) / 64) >= 256) launch_gather<false, 4, 2, 8, 2>(a, M, s);
     else if (M / 256 * ((a.N + 31) / 32) >= 256) launch_gather<false, 2, 2, 8, 4>(a, M, s);
     else launch_gather<false, 2, 1, 4, 8>(a, M, s);
