@@ -427,10 +427,10 @@ ups_status ups_batch_fallback_run(ups_context *ctx, ups_batch *b, ups_icp_result
  * n_yaw n_xy^2 <= 65535, left holding every candidate's score.  Builds the
  * batch's pyramids from the level-0 surfel images first; enqueues only
  * kernels.  The best poses can start ups_register_batch.  Scratch: tables of
- * the keyframes' points, about 8 bytes per keyframe pixel at level 0, in the
+ * the keyframes' points, at most 8 bytes per keyframe pixel at level 0, in the
  * batch's scratch for normals where its items have depth images, else laid out
- * by ups_batch_create if the memory is there (without them the search reads
- * the keyframes' images, the same scores, slower). */
+ * by ups_batch_create if the memory is there (where the search has none it
+ * reads the keyframes' images, with the same scores). */
 typedef struct {
     int32_t level;
     int32_t n_yaw, n_xy;

@@ -49,7 +49,8 @@ struct ups_batch {
     // then reads the keyframes' images)
     char *grid_points = nullptr, *grid_own = nullptr;
     int64_t *d_points_off = nullptr;  // [4][n] byte offsets of the tables in it
-    bool points_level[4] = {false, false, false, false};  // levels that have them
+    int64_t points_bytes[4] = {0, 0, 0, 0};  // of a level's tables, where it has them
+    int64_t scan_pixels[4] = {0, 0, 0, 0};   // of a level of all scans
     RegState *state = nullptr;    // [n][2]
     double *partials = nullptr;   // [n][2][kPartialStride][pstride]
     // batched normals
@@ -166,6 +167,24 @@ bool blocks_may_leave(int tiles, const ups_icp_params &p) {
 int tiles_per_block(int tiles, const ups_icp_params &p) {
     if (tiles >= 24 * 1024) return 4;
     return tiles >= 12 * 1024 && p.precision != UPS_PREC_F32 ? 2 : 1;
+}
+
+// Whether a search takes the keyframes' tables (tables_fit, and one candidate
+// pixel a byte).  They save a candidate a quarter of its instructions, but an entry has half as
+// many bytes again as a surfel and has to be filled: 24 candidate pixels an
+// entry pay for that.  And the tables of the registrations in
+// flight have to stay in an XCD's L2: at most 2 MB each, but 0.5 MB, or 4 MB in
+// all, where the keyframes have more than 1.5 entries a scan pixel, so that
+// neighbouring pixels meet in few cache lines.  us a search of 64 pairs with
+// the images / the tables:
+//   scan on keyframe, level, table      36 x 9    12 x 9     4 x 9     8 x 1 candidates
+//   64 x 512 on the same, 1, 0.2 MB        325/262   135/115     91/70     53/53
+//   128 x 2048 on the same, 1, 1.6 MB    2386/1952   931/811   409/392   232/248
+//   256 x 2048 on the same, 1, 3.1 MB    4839/4098 1912/1759   823/932   458/465
+//   128 x 1024 on 128 x 2048, 2, 0.4 MB    442/394   232/227   157/138   119/120
+//   128 x 1024 on 128 x 2048, 1, 1.6 MB  1469/1758   629/804   300/359   148/180
+bool tables_fit(int64_t bytes, int64_t scan_pixels, int64_t n) {
+    return bytes <= 36 * scan_pixels ? bytes <= n * 2000000 : bytes <= std::max<int64_t>(n * 500000, 4000000);
 }
 
 // The pyramids a register / grid-search call builds: every image's, or in
@@ -372,12 +391,19 @@ ups_status ups_batch_create(ups_context *ctx, int32_t n, const ups_batch_item *i
     std::vector<int64_t> points_off((size_t)4 * n, 0);
     for (int l = 1; l < L; l++) {
         // entries are numbered in 24 bits
-        b->points_level[l] = true;
-        for (int k = 0; k < n; k++) b->points_level[l] &= grid_points_bytes(hi[k].kg[l]) <= (24ull << 24);
-        for (int k = 0; b->points_level[l] && k < n; k++) {
-            points_off[(size_t)l * n + k] = points_total;
-            points_total += (int64_t)(grid_points_bytes(hi[k].kg[l]) + 15) / 16 * 16;
+        bool fits = true;
+        for (int k = 0; k < n; k++) {
+            fits &= grid_points_bytes(hi[k].kg[l]) <= (24ull << 24);
+            b->scan_pixels[l] += (int64_t)hi[k].sg[l].rows * hi[k].sg[l].cols;
         }
+        int64_t bytes = 0;
+        for (int k = 0; k < n; k++) {
+            points_off[(size_t)l * n + k] = points_total + bytes;
+            bytes += (int64_t)(grid_points_bytes(hi[k].kg[l]) + 15) / 16 * 16;
+        }
+        if (!fits || !tables_fit(bytes, b->scan_pixels[l], n)) continue;
+        b->points_bytes[l] = bytes;
+        points_total += bytes;
     }
     alloc((void **)&b->d_points_off, points_off.size() * sizeof(int64_t));
     alloc((void **)&b->state, (size_t)n * 2 * sizeof(RegState));
@@ -815,8 +841,9 @@ ups_status ups_batch_grid_search(ups_context *ctx, ups_batch *b, const ups_grid_
     g.xy_step = gp->xy_step;
     g.d_max2 = gp->d_max * gp->d_max;
     g.cos_theta = gp->cos_theta_max;
-    // the general kernel reads the keyframe's images
-    g.points = b->points_level[l] && gp->n_xy <= 5 ? b->grid_points : nullptr;
+    // the general kernel (n_xy > 5) reads the keyframe's images
+    const bool tables = gp->n_xy <= 5 && b->points_bytes[l] > 0 && b->points_bytes[l] <= b->scan_pixels[l] * g.C;
+    g.points = tables ? b->grid_points : nullptr;
     g.points_off = b->d_points_off + (size_t)l * n;
     return launch_grid_search(b->d_inst, b->d_tile_start + l * (n + 1), b->d_tile_of + b->tile_of_off[l], n, b->K[l],
                               b->total_tiles[l], base_d, g, scores_d, best_d, best_score_d, s);

@@ -190,8 +190,8 @@ __global__ __launch_bounds__(kBlock) void k_grid_points(const Inst *__restrict__
 // blocks share a tile, so its keyframe image is fetched into L2 once for all
 // chunks that run together.
 // Bound by the vector instructions of a candidate, mostly the two arctangents.
-// POINTS: the keyframe comes from the table of k_grid_points (levels 1 and
-// up): no ray tables, no surfel test, one address: 227 us against 300
+// POINTS: the keyframe comes from the table of k_grid_points (levels 1 and up,
+// where the batch's sizes and the candidates are such that it pays): no ray tables, no surfel test, one address: 227 us against 300
 // for 64 registrations x 324 candidates at level 2, with 7.7 us to fill the table.
 template <int NXY, int YB, bool POINTS>
 __global__ __launch_bounds__(kBlock) void k_grid_score_yaw(const Inst *__restrict__ insts,
@@ -243,7 +243,8 @@ __global__ __launch_bounds__(kBlock) void k_grid_score_yaw(const Inst *__restric
         const float2 e = lds_uniform(sg.lut_row, i << sg.lshift);
         const float2 ca = ldg_u(sg.lut_col, (uint32_t)j << sg.lshift);
         const bool sok = surfel_ok(sg, s2);
-        if (!__builtin_amdgcn_ballot_w64(sok)) continue;  // no surfel in this wavefront's pixels
+        if constexpr (POINTS)
+            if (!__builtin_amdgcn_ballot_w64(sok)) continue;  // no surfel in this wavefront's pixels
         const float3 u = make_float3(e.x * ca.x, e.x * ca.y, e.y);
         const float3 p3 = make_float3(s2.w * u.x, s2.w * u.y, s2.w * u.z);
         const float3 n2 = make_float3(s2.x, s2.y, s2.z);
@@ -364,7 +365,8 @@ size_t grid_points_bytes(const DGeom &kg) { return ((size_t)kg.rows * (kg.cols +
 ups_status launch_grid_search(const Inst *insts, const int *tile_start_l, const unsigned *tile_of, int n, int K,
                               int tiles, const ups_pose *base, const GridArgs &g, int *scores, ups_pose *best,
                               int *best_score, hipStream_t s) {
-    hipLaunchKernelGGL(k_grid_points, dim3(32, n), dim3(kBlock), 0, s, insts, g, scores);
+    const int fill = g.points ? 32 : (std::min(g.C, 8192) + kBlock - 1) / kBlock;  // or only the scores to clear
+    hipLaunchKernelGGL(k_grid_points, dim3(fill, n), dim3(kBlock), 0, s, insts, g, scores);
     UPS_CHECK_HIP(hipGetLastError());
     if (tiles > 0) {
         // yaws per block: as many as keep 36 or fewer candidates per block

@@ -270,7 +270,7 @@ def test_keyframe_tables_take_the_normals_scratch(gpu_lib):
     bare = [{k: v for k, v in it.items() if "depth" not in k} for it in full]
     params = gpu_lib.IcpParams(levels=levels, iters=(4, 4, 4))
     taken = {}
-    gp = gpu_lib.GridParams(level=1, n_yaw=4, n_xy=2, xy_step=0.5, d_max=1.0)
+    gp = gpu_lib.GridParams(level=1, n_yaw=12, n_xy=2, xy_step=0.5, d_max=1.0)
     found = {}
     for name, items in (("warm", full), ("depth", full), ("bare", bare)):
         torch.cuda.synchronize()
@@ -295,3 +295,37 @@ def test_keyframe_tables_take_the_normals_scratch(gpu_lib):
           f"normals {normals / 2**20:.1f}, tables {tables / 2**20:.1f}")
     # the normals' lists of tiles, and the allocator's granularity of 2 MiB in a few allocations
     assert taken["depth"] - taken["bare"] <= normals - tables + (16 << 20)
+
+
+def test_searches_with_and_without_tables(gpu_lib):
+    """Whether a search takes the keyframes' tables depends on its candidates
+    and on the batch's sizes; its scores do not: 12 yaws (images) and the same
+    with four equal translations (tables); scans of half the keyframe's columns
+    in a batch of two (tables of 3.2 MB) and of three (images)."""
+    pairs = [W.batch_pair(k, base_seed=5_600_000, max_angle=math.radians(40.0), size=(128, 2048)) for k in range(3)]
+    ctx = gpu_lib.Context(0, max_pixels=128 * 2048, max_batch=3, max_batch_pixels=3 * 128 * 2048)
+    items = _items(pairs)
+    for it in items:
+        gpu_lib.panorama_normals(ctx, it["scan_geom"], it["scan_depth"], it["scan_surfel"])
+        gpu_lib.panorama_normals(ctx, it["kf_geom"], it["kf_depth"], it["kf_surfel"])
+    half = []
+    for it in items:
+        g = it["scan_geom"]
+        h = synth.Geom(g.rows, g.cols // 2, g.el_top, g.d_el, g.r_min, g.r_max)
+        half.append(dict(it, scan_geom=h, scan_surfel=it["scan_surfel"][:, ::2].contiguous(), scan_depth=None))
+    params = gpu_lib.IcpParams(levels=3, iters=(1, 1, 1))
+    for group in (items, half):
+        b = gpu_lib.Batch(ctx, group, params)
+        for level in (1, 2):
+            one, four = (b.grid_search(gpu_lib.GridParams(level=level, n_yaw=12, n_xy=k, xy_step=0.0, d_max=1.0))[2]
+                         .cpu().numpy().reshape(3, 12, k * k) for k in (1, 2))
+            assert one.max() > 100 and np.array_equal(np.repeat(one, 4, axis=2), four)
+        b.close()
+    scores = []
+    for group in (half[:2], half):
+        b = gpu_lib.Batch(ctx, group, params)
+        gp = gpu_lib.GridParams(level=1, n_yaw=36, n_xy=2, xy_step=0.5, d_max=1.0)
+        scores.append(b.grid_search(gp)[2].cpu().numpy()[:2])
+        b.close()
+    assert scores[0].max() > 100 and np.array_equal(*scores)
+    ctx.close()
