@@ -191,8 +191,9 @@ __global__ __launch_bounds__(kBlock) void k_grid_points(const Inst *__restrict__
 // chunks that run together.
 // Bound by the vector instructions of a candidate, mostly the two arctangents.
 // POINTS: the keyframe comes from the table of k_grid_points (levels 1 and up,
-// where the batch's sizes and the candidates are such that it pays): no ray tables, no surfel test, one address: 227 us against 300
-// for 64 registrations x 324 candidates at level 2, with 7.7 us to fill the table.
+// where the batch's sizes and the candidates are such that it pays): no ray
+// tables, no surfel test, one address: 227 us against 300 for 64 registrations
+// x 324 candidates at level 2, with 7.7 us to fill the table.
 template <int NXY, int YB, bool POINTS>
 __global__ __launch_bounds__(kBlock) void k_grid_score_yaw(const Inst *__restrict__ insts,
                                                            const unsigned *__restrict__ tile_of, int K,
