@@ -446,7 +446,7 @@ static ups_status wgrad_sums(const ConvShape &c, const uint16_t *x, const uint16
     const bool narrow = c.cin <= 3;
     const int row_tiles = narrow ? 1 : cdiv(9 * c.cin, kRowTile);
     // 64 channels a block: half the staged windows of 32 for the same products (batch 256, 32 -> 64 and 64 -> 96
-    // channels: 25.7 and 26.6 us against 36.0 and 36.9); 32 where there are no more
+    // channels: 26.5 and 27.7 us against 36.0 and 36.9); 32 where there are no more
     const int nf = narrow || c.cout <= 32 ? 2 : 4;
     const int chunk = split_chunk(c);
     // narrow form: four wavefronts a block where a split is one step of theirs, or where several blocks share a split
